@@ -1,7 +1,7 @@
 // Tile code: one workgroup evaluates one tile of blockDim.x * P consecutive
 // points; each wave takes 64 * P of them and each thread P (see Lane), laid
 // out so that every SoA field is read and written as whole contiguous runs
-// (16-byte vector accesses per lane when the call's pointers allow it).  The
+// (16-byte vector accesses per lane, whatever the rows' alignment).  The
 // flux Jacobian blocks, which are stored point-major (K*K contiguous values
 // per point), are staged through a per-wave LDS region and written out as
 // contiguous runs of 16-byte stores.
@@ -15,7 +15,6 @@ constexpr int kWave = 64;
 
 enum : int32_t {
     kFlagInPlace = 1,  // K -> K transform with output == input: skip the rho store
-    kFlagVector = 2,   // every base pointer and row stride allows 16-byte access
     kFlagRight = 4,    // characteristic product with R (else with L)
     kFlagOneDir = 8,   // flux of direction Args::dir only, as K fields
 };
@@ -40,8 +39,21 @@ struct Args {
     Gas gas;
 };
 
+// W values at a global address that is aligned to one value only: a packed
+// (fields, n) tensor with an odd n or a view that starts inside a row has no
+// 16-byte-aligned rows.  gfx950's multi-dword global accesses ask for dword
+// alignment alone, so such rows take the same wide accesses as aligned ones.
+// Element-wise accesses for them (lane stride W values) cost 2D flux FP32 on
+// 1 000 003 points, packed in and out, 80 us against 12.6 us this way (10.4 us
+// with aligned rows), the fused 2D pass on 8 M points 1256 against 637 us in
+// FP64 and 1288 against 287 us in FP32.  Packed inputs with aligned outputs
+// run as fast as aligned ones; what is left with packed outputs is the cache
+// lines shared by two runs.
 template <typename T, int N>
-using vec_t = T __attribute__((ext_vector_type(N)));
+using vec_t = T __attribute__((ext_vector_type(N), aligned(sizeof(T))));
+// The same values in LDS, where every staged run starts on 16 bytes.
+template <typename T, int N>
+using lds_vec_t = T __attribute__((ext_vector_type(N)));
 
 // Points per chunk and chunks per thread.  A chunk is the unit of one
 // vector access and of the FP64 per-point state held in registers at one
@@ -69,9 +81,9 @@ __device__ __forceinline__ V get(const V *p)
 
 // Load the W consecutive values at p (cnt of them valid) widened to FP64.
 template <typename T, int W, bool NTL = false>
-__device__ __forceinline__ void load_chunk(const T *__restrict__ p, int cnt, bool vec, double *x)
+__device__ __forceinline__ void load_chunk(const T *__restrict__ p, int cnt, double *x)
 {
-    if (vec && cnt == W) {
+    if (cnt == W) {
         if constexpr (W == 1) {
             x[0] = (double)get<NTL, T>(p);
         } else {
@@ -135,9 +147,9 @@ __device__ __forceinline__ void put(V *p, V v)
 
 // Store W consecutive FP64 values at p, rounded to T (cnt of them valid).
 template <typename T, int W, int NT>
-__device__ __forceinline__ void store_chunk(T *__restrict__ p, int cnt, bool vec, const double *x)
+__device__ __forceinline__ void store_chunk(T *__restrict__ p, int cnt, const double *x)
 {
-    if (vec && cnt == W) {
+    if (cnt == W) {
         if constexpr (W == 1) {
             put<NT, T>(p, (T)x[0]);
         } else {
@@ -168,7 +180,6 @@ struct Lane {
     int64_t i;     // first point of this thread's first chunk
     int64_t left;  // points from i to the end of the range
     int lane;
-    bool vec;
 
     __device__ __forceinline__ Lane(const Args &a, int64_t tile0)
     {
@@ -176,7 +187,6 @@ struct Lane {
         const int wave = threadIdx.x / kWave;
         i = tile0 + (int64_t)wave * kWave * P + (int64_t)lane * W;
         left = a.n - i;
-        vec = (a.flags & kFlagVector) != 0;
     }
 
     __device__ __forceinline__ bool any() const { return left > 0; }
@@ -197,7 +207,7 @@ struct Lane {
     __device__ __forceinline__ void load(const void *base, int64_t ld, int field, int c, double *x) const
     {
         const T *b = static_cast<const T *>(base) + i + (int64_t)field * ld + c * CS;
-        load_chunk<T, W, NTL>(b, count(c), vec, x);
+        load_chunk<T, W, NTL>(b, count(c), x);
     }
 
     // Chunk c of `FIELDS` consecutive fields into x[field][W].
@@ -212,7 +222,7 @@ struct Lane {
     __device__ __forceinline__ void store(void *base, int64_t ld, int field, int c, const double *x) const
     {
         T *b = static_cast<T *>(base) + i + (int64_t)field * ld + c * CS;
-        store_chunk<T, W, NT>(b, count(c), vec, x);
+        store_chunk<T, W, NT>(b, count(c), x);
     }
 };
 
@@ -752,20 +762,16 @@ __device__ __forceinline__ void tile_adjoint(const Args &a, int64_t tile0)
 // ------------------------------------------------------------ Jacobian blocks
 
 // Copy the wave's staged blocks (count elements of T, contiguous in LDS and
-// in global memory) with lane-contiguous 16-byte stores when allowed.
+// in global memory) with lane-contiguous 16-byte stores.
 template <typename T, int NT>
-__device__ __forceinline__ void wave_copy_out(const T *lds, T *dst, int count, bool vec, int lane)
+__device__ __forceinline__ void wave_copy_out(const T *lds, T *dst, int count, int lane)
 {
-    if (vec) {
-        constexpr int W = 16 / (int)sizeof(T);
-        const int chunks = count / W;
-        const vec_t<T, W> *src = reinterpret_cast<const vec_t<T, W> *>(lds);
-        vec_t<T, W> *out = reinterpret_cast<vec_t<T, W> *>(dst);
-        for (int c = lane; c < chunks; c += kWave) put<NT, vec_t<T, W>>(out + c, src[c]);
-        for (int e = chunks * W + lane; e < count; e += kWave) put<NT, T>(dst + e, lds[e]);
-    } else {
-        for (int e = lane; e < count; e += kWave) put<NT, T>(dst + e, lds[e]);
-    }
+    constexpr int W = 16 / (int)sizeof(T);
+    const int chunks = count / W;
+    const lds_vec_t<T, W> *src = reinterpret_cast<const lds_vec_t<T, W> *>(lds);
+    vec_t<T, W> *out = reinterpret_cast<vec_t<T, W> *>(dst);
+    for (int c = lane; c < chunks; c += kWave) put<NT, vec_t<T, W>>(out + c, src[c]);
+    for (int e = chunks * W + lane; e < count; e += kWave) put<NT, T>(dst + e, lds[e]);
 }
 
 // Stage this wave's 64 * P blocks of one K x K matrix per point in LDS
@@ -790,7 +796,7 @@ __device__ __forceinline__ void stage_blocks(const Lane<T, P, NT> &L, T *region,
         __builtin_amdgcn_sched_barrier(0);
     }
     __syncthreads();
-    if (wave_pts > 0) wave_copy_out<T, NT>(region, dst, wave_pts * KK, L.vec, L.lane);
+    if (wave_pts > 0) wave_copy_out<T, NT>(region, dst, wave_pts * KK, L.lane);
     __syncthreads();
 }
 

@@ -241,8 +241,6 @@ struct Call {
     Range ranges[8];            // field sets of the call, for alias checks
     int nranges = 0;
     bool inplace_ok = false;    // K -> K transform
-    size_t unit_out0 = 1;       // elements per point of out0 (K*K for blocks)
-    size_t unit_out1 = 1;       // elements per point of out1 (K*K for blocks)
 };
 
 // Register one field set: checks NULL, ld and alignment.
@@ -277,22 +275,6 @@ int check_alias(const Call &c)
             return fail(FDBB_EALIAS, "input and output field sets overlap");
         }
     return FDBB_OK;
-}
-
-// 16-byte access is allowed when every base is 16-byte aligned and every row
-// stride is a multiple of 16 bytes.
-bool vector_ok(const Call &c)
-{
-    const size_t es = elem_size(c.dtype);
-    const void *bases[6] = {c.a.in0, c.a.in1, c.a.in2, c.a.out0, c.a.out1, c.a.out2};
-    const int64_t lds[6] = {c.a.ld_in0, c.a.ld_in1, c.a.ld_in2, c.a.ld_out0, c.a.ld_out1, c.a.ld_out2};
-    const size_t units[6] = {1, 1, 1, c.unit_out0, c.unit_out1, 1};
-    for (int k = 0; k < 6; ++k) {
-        if (!bases[k]) continue;
-        if ((uintptr_t)bases[k] % 16 != 0) return false;
-        if (((size_t)lds[k] * units[k] * es) % 16 != 0) return false;
-    }
-    return true;
 }
 
 int family_of(int op)
@@ -386,7 +368,6 @@ int launch(Call &c, void *stream)
     if (c.a.n == 0) return FDBB_OK;
     int rc = check_alias(c);
     if (rc) return rc;
-    if (vector_ok(c)) c.a.flags |= kFlagVector;
 
     const Config cfg = get_config(c.op, c.dim, c.dtype, c.a.n);
     const void *fn = kernel_for(c.op, c.dim, c.dtype, cfg.ppt, cfg.nt != 0);
@@ -479,7 +460,6 @@ int build_call(Call &c, const fdbb_task &t, int mode = 0)
         break;
     case FDBB_OP_EIGENVECTORS:
         if (!t.out0 && !t.out1 && t.n > 0) return fail(FDBB_EINVAL, "L and R must not both be NULL");
-        c.unit_out0 = c.unit_out1 = (size_t)K * K;
         a.in0 = t.in0, a.ld_in0 = t.ld_in0;
         a.out0 = t.out0, a.ld_out0 = t.ld_out0, a.out1 = t.out1, a.ld_out1 = t.ld_out1;
         if ((rc = add_fields(c, t.in0, t.ld_in0, K, 1, true, true, "U"))) return rc;
@@ -526,14 +506,12 @@ int build_call(Call &c, const fdbb_task &t, int mode = 0)
         break;
     case FDBB_OP_FLUX_JACOBIAN:
         // The Jacobian blocks travel in out1 of the fused kernel.
-        c.unit_out1 = (size_t)K * K;
         a.in0 = t.in0, a.ld_in0 = t.ld_in0, a.out1 = t.out0, a.ld_out1 = t.ld_out0;
         if ((rc = add_fields(c, t.in0, t.ld_in0, K, 1, true, true, "U"))) return rc;
         if ((rc = add_fields(c, t.out0, t.ld_out0, D, (int64_t)K * K, false, true, "A"))) return rc;
         break;
     case FDBB_OP_FUSED:
         if (!t.out0 && !t.out1 && !t.out2 && t.n > 0) return fail(FDBB_EINVAL, "F, A and R must not all be NULL");
-        c.unit_out1 = (size_t)K * K;
         a.in0 = t.in0, a.ld_in0 = t.ld_in0;
         a.out0 = t.out0, a.ld_out0 = t.ld_out0;
         a.out1 = t.out1, a.ld_out1 = t.ld_out1;
@@ -966,7 +944,6 @@ int fill_table(const fdbb_task *tasks, int ntasks, int cap, int block, int ppt, 
         if (rc) return fail(rc, "task " + std::to_string(b) + ": " + g_last_error);
         rc = check_alias(c);
         if (rc) return fail(rc, "task " + std::to_string(b) + ": " + g_last_error);
-        if (vector_ok(c)) c.a.flags |= kFlagVector;
         const bool jac = tasks[b].op == FDBB_OP_FLUX_JACOBIAN || (tasks[b].op == FDBB_OP_FUSED && tasks[b].out1);
         if (jac) r.lds = std::max(r.lds, lds_bytes(tasks[b].op, tasks[b].dim, tasks[b].dtype, block, ppt));
         for (int k = 0; k < c.nranges; ++k) {
