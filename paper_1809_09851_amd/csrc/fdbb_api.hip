@@ -334,6 +334,53 @@ size_t lds_bytes(int op, int dim, int dtype, int block, int ppt)
     return (size_t)block * ppt * K * K * elem_size(dtype);
 }
 
+// Values one point writes (every output of the op).
+int written_values(int op, int dim)
+{
+    const int K = dim + 2;
+    switch (op) {
+    case FDBB_OP_EOS: return 2;
+    case FDBB_OP_EOS_PVT: return 3;
+    case FDBB_OP_V_MAG2: return 1;
+    case FDBB_OP_FLUX:
+    case FDBB_OP_VISCOUS_FLUX: return K * dim;
+    case FDBB_OP_RIEMANN: return 2 * dim + 1;
+    default: return K;
+    }
+}
+
+// Waves of a pointwise kernel that may be resident on a compute unit.  A
+// wave writes as many rows as its op has output fields, far apart in memory,
+// so every resident wave adds that many open DRAM rows; past about 57 KB of
+// output in flight per compute unit (900 B per lane) more waves only make
+// the rows of different fields displace each other.  3D flux FP64 (120 B
+// written per point) at 12 000 017 points: 8 waves 301 us, 16 waves 316,
+// unlimited (32) 353; 2D flux FP64 (64 B): 10 waves 178, unlimited 200;
+// 3D Riemann invariants FP64 (56 B): 12-16 waves 1 % off the best, unlimited
+// 6 %.  Below 8 waves the loads of the next waves no longer cover the
+// latency (3D flux FP64 at 6 waves: 310 us; 1D flux FP32 at 8: 2.4 times
+// slower), and ops that write 32 B or less keep every wave.
+constexpr int kMaxWaves = 32, kMinWaves = 8;
+constexpr int kWrittenPerLane = 900;
+
+int resident_waves(int op, int dim, int dtype, int ppt)
+{
+    const int per_lane = written_values(op, dim) * (int)elem_size(dtype) * ppt;
+    const int waves = std::max(kMinWaves / ppt, (kWrittenPerLane + per_lane / 2) / per_lane);
+    return waves >= kMaxWaves - 4 ? kMaxWaves : std::max(1, waves);
+}
+
+// Dynamic LDS that keeps at most `waves` waves in workgroups of `block`
+// threads resident on a compute unit (0: no limit): the kernel does not
+// touch it, it only takes the space of the workgroups that should wait.
+// Allocations are made in steps of 1280 bytes.
+size_t residency_lds(int waves, int block, const DeviceInfo &dev)
+{
+    if (waves >= kMaxWaves) return 0;
+    const int groups = std::max(1, (waves * 64 + block / 2) / block);
+    return dev.lds_max / groups / 1280 * 1280;
+}
+
 // Kernels whose dynamic-LDS limit has been raised on a device, as an
 // open-addressed set of (kernel address | device << 56) keys.  The limit is
 // raised once, to the device maximum, the first time a kernel needs more
@@ -377,7 +424,10 @@ int launch(Call &c, void *stream)
     if (rc) return rc;
     const bool needs_lds = (c.op == FDBB_OP_FLUX_JACOBIAN) || (c.op == FDBB_OP_FUSED && c.a.out1) ||
                            (c.op == FDBB_OP_EIGENVECTORS);
-    const size_t lds = needs_lds ? lds_bytes(c.op, c.dim, c.dtype, cfg.block, cfg.ppt) : 0;
+    size_t lds = 0;
+    if (needs_lds) lds = lds_bytes(c.op, c.dim, c.dtype, cfg.block, cfg.ppt);
+    else if (!stages_blocks(c.op))
+        lds = residency_lds(resident_waves(c.op, c.dim, c.dtype, cfg.ppt), cfg.block, dev);
     rc = set_lds_attr(fn, lds, dev);
     if (rc) return rc;
 
