@@ -517,11 +517,12 @@ __device__ __forceinline__ void store_flux(const Lane<T, P, NT> &L, const State<
     }
 }
 
-// The K components of F_dir alone (field r = component r), of W points.
-// dir is uniform over the launch, so the test below does not diverge.
+// The K components of F_dir alone, of W points: component r goes to field
+// first + r * step.  dir is uniform over the workgroup, so the test below
+// does not diverge.
 template <int D, typename T, int P, int NT>
 __device__ __forceinline__ void store_flux_dir(const Lane<T, P, NT> &L, const State<D> *s, int c, int dir,
-                                               void *F, int64_t ldF)
+                                               void *F, int64_t ldF, int first, int step)
 {
     constexpr int W = Lane<T, P, NT>::W;
 #pragma unroll
@@ -532,15 +533,16 @@ __device__ __forceinline__ void store_flux_dir(const Lane<T, P, NT> &L, const St
             double f[W];
 #pragma unroll
             for (int j = 0; j < W; ++j) f[j] = flux_entry<D>(s[j], r, d);
-            L.store(F, ldF, r, c, f);
+            L.store(F, ldF, first + r * step, c, f);
         }
     }
 }
 
-// Riemann invariants of every direction and the entropy, of W points.
+// Riemann invariants of W points: those of the directions in `rows`, and the
+// entropy with direction 0.
 template <int D, typename T, int P, int NT>
 __device__ __forceinline__ void store_riemann(const Args &a, const Lane<T, P, NT> &L, const State<D> *s, int c,
-                                              void *R, int64_t ldR)
+                                              void *R, int64_t ldR, uint32_t rows)
 {
     constexpr int W = Lane<T, P, NT>::W;
     double t[W];
@@ -548,6 +550,7 @@ __device__ __forceinline__ void store_riemann(const Args &a, const Lane<T, P, NT
     for (int j = 0; j < W; ++j) t[j] = a.gas.two_inv_g1 * sound_speed<D>(a.gas, s[j]);
 #pragma unroll
     for (int d = 0; d < D; ++d) {
+        if (!(rows >> d & 1u)) continue;
         double wm[W], wp[W];
 #pragma unroll
         for (int j = 0; j < W; ++j) {
@@ -557,6 +560,7 @@ __device__ __forceinline__ void store_riemann(const Args &a, const Lane<T, P, NT
         L.store(R, ldR, 2 * d, c, wm);
         L.store(R, ldR, 2 * d + 1, c, wp);
     }
+    if (!(rows & 1u)) return;
     double en[W];
 #pragma unroll
     for (int j = 0; j < W; ++j) en[j] = entropy<D, sizeof(T) == 4>(a.gas, s[j]);
@@ -584,7 +588,7 @@ __device__ __forceinline__ void tile_flux(const Args &a, int64_t tile0)
             for (int k = 0; k < K; ++k) uj[k] = u[c][k][j];
             s[j] = make_state<D>(a.gas, uj);
         }
-        if (a.flags & kFlagOneDir) store_flux_dir<D, T, P, NT>(L, s, c, a.dir, a.out0, a.ld_out0);
+        if (a.flags & kFlagOneDir) store_flux_dir<D, T, P, NT>(L, s, c, a.dir, a.out0, a.ld_out0, 0, 1);
         else store_flux<D, T, P, NT>(L, s, c, a.out0, a.ld_out0);
     }
 }
@@ -610,7 +614,7 @@ __device__ __forceinline__ void tile_riemann(const Args &a, int64_t tile0)
             for (int k = 0; k < K; ++k) uj[k] = u[c][k][j];
             s[j] = make_state<D>(a.gas, uj);
         }
-        store_riemann<D, T, P, NT>(a, L, s, c, a.out0, a.ld_out0);
+        store_riemann<D, T, P, NT>(a, L, s, c, a.out0, a.ld_out0, (1u << D) - 1u);
     }
 }
 
@@ -808,15 +812,23 @@ __device__ __forceinline__ int wave_points(int64_t n, int64_t wave0)
     return left <= 0 ? 0 : (left >= kWave * P ? kWave * P : (int)left);
 }
 
-// The fused pass: flux tensor (out0, may be NULL), Jacobian blocks (out1,
-// may be NULL) and Riemann invariants (out2, may be NULL) of the same state.
-// Flux and invariants are stored chunk by chunk from the full state; the
-// Jacobian keeps only v, H and phi of each point, and its blocks go through
-// `lds`, this workgroup's staging area of blockDim.x * P * K * K values
-// (each wave uses its own 64 * P blocks).  Every thread of the workgroup
-// must call this (it holds barriers).
+// Parts of a tile's output, as bits: block arrays 0..5 (the Jacobian of
+// direction d: bit d; L_d and R_d: bits 2d and 2d + 1) and, for the fused
+// pass, the flux rows and invariants of direction d (bit 8 + d).
+constexpr uint32_t kPartFields = 8;
+template <int D>
+constexpr uint32_t all_directions = (1u << D) - 1u;
+
+// The fused pass over one tile: the parts in `mask` of the flux tensor
+// (out0, may be NULL), Jacobian blocks (out1, may be NULL) and Riemann
+// invariants (out2, may be NULL) of the same state.  Flux and invariants are
+// stored chunk by chunk from the full state; the Jacobian keeps only v, H and
+// phi of each point, and its blocks go through `lds`, this workgroup's
+// staging area of blockDim.x * P * K * K values (each wave uses its own
+// 64 * P blocks).  Every thread of the workgroup must call this (it holds
+// barriers), with the same mask.
 template <int D, typename T, int P, int NT>
-__device__ __forceinline__ void tile_fused(const Args &a, int64_t tile0, T *lds)
+__device__ __forceinline__ void tile_fused(const Args &a, int64_t tile0, uint32_t mask, T *lds)
 {
     constexpr int K = D + 2;
     constexpr int KK = K * K;
@@ -825,6 +837,7 @@ __device__ __forceinline__ void tile_fused(const Args &a, int64_t tile0, T *lds)
     const L_t L(a, tile0);
     const int wave = threadIdx.x / kWave;
     const int64_t wave0 = tile0 + (int64_t)wave * kWave * P;
+    const uint32_t rows = (mask >> kPartFields) & all_directions<D>;
 
     double u[NC][K][W];
 #pragma unroll
@@ -846,31 +859,39 @@ __device__ __forceinline__ void tile_fused(const Args &a, int64_t tile0, T *lds)
             jH[q] = (s[j].E + s[j].p) * s[j].rinv;
             jphi[q] = a.gas.half_g1 * s[j].q;
         }
-        if (L.any()) {
-            if (a.out0) store_flux<D, T, P, NT>(L, s, c, a.out0, a.ld_out0);
-            if (a.out2) store_riemann<D, T, P, NT>(a, L, s, c, a.out2, a.ld_out2);
+        if (rows && L.any()) {
+            if (a.out0) {
+                if (rows == all_directions<D>) {
+                    store_flux<D, T, P, NT>(L, s, c, a.out0, a.ld_out0);
+                } else {
+#pragma unroll
+                    for (int d = 0; d < D; ++d)
+                        if (rows >> d & 1u) store_flux_dir<D, T, P, NT>(L, s, c, d, a.out0, a.ld_out0, d, D);
+                }
+            }
+            if (a.out2) store_riemann<D, T, P, NT>(a, L, s, c, a.out2, a.ld_out2, rows);
         }
         __builtin_amdgcn_sched_barrier(0);  // one chunk's state at a time
     }
 
-    if (a.out1) {
-        T *region = lds + (size_t)wave * kWave * P * KK;
-        const int wave_pts = wave_points<P>(a.n, wave0);
-        T *A = static_cast<T *>(a.out1);
+    if (!a.out1) return;
+    T *region = lds + (size_t)wave * kWave * P * KK;
+    const int wave_pts = wave_points<P>(a.n, wave0);
+    T *A = static_cast<T *>(a.out1);
 #pragma unroll
-        for (int d = 0; d < D; ++d)
-            stage_blocks<D, T, P, NT>(L, region, A + (d * a.ld_out1 + wave0) * KK, wave_pts,
-                                      [&](int q, int r, int c) {
-                                          return jacobian_entry<D>(a.gas, jv[q], jphi[q], jH[q], d, r, c);
-                                      });
+    for (int d = 0; d < D; ++d) {
+        if (!(mask >> d & 1u)) continue;
+        stage_blocks<D, T, P, NT>(L, region, A + (d * a.ld_out1 + wave0) * KK, wave_pts, [&](int q, int r, int c) {
+            return jacobian_entry<D>(a.gas, jv[q], jphi[q], jH[q], d, r, c);
+        });
     }
 }
 
-// Characteristic decomposition of every direction: left eigenvector blocks
-// L_d (out0, may be NULL) and right eigenvector blocks R_d (out1, may be
-// NULL), point-major K x K blocks like the Jacobian, staged through LDS.
+// Characteristic decomposition over one tile: left eigenvector blocks L_d
+// (out0) and right eigenvector blocks R_d (out1) of the parts in `mask`,
+// point-major K x K blocks like the Jacobian, staged through LDS.
 template <int D, typename T, int P, int NT>
-__device__ __forceinline__ void tile_eigen(const Args &a, int64_t tile0, T *lds)
+__device__ __forceinline__ void tile_eigen(const Args &a, int64_t tile0, uint32_t mask, T *lds)
 {
     constexpr int K = D + 2;
     constexpr int KK = K * K;
@@ -903,15 +924,43 @@ __device__ __forceinline__ void tile_eigen(const Args &a, int64_t tile0, T *lds)
     const int wave_pts = wave_points<P>(a.n, wave0);
 #pragma unroll
     for (int d = 0; d < D; ++d) {
-        if (a.out0)
+        if (mask >> (2 * d) & 1u)
             stage_blocks<D, T, P, NT>(L, region, static_cast<T *>(a.out0) + (d * a.ld_out0 + wave0) * KK,
                                       wave_pts,
                                       [&](int q, int r, int c) { return left_entry<D>(v[q], w[q], d, r, c); });
-        if (a.out1)
+        if (mask >> (2 * d + 1) & 1u)
             stage_blocks<D, T, P, NT>(L, region, static_cast<T *>(a.out1) + (d * a.ld_out1 + wave0) * KK,
                                       wave_pts,
                                       [&](int q, int r, int c) { return right_entry<D>(v[q], w[q], d, r, c); });
     }
+}
+
+// How a launch deals the parts of its tiles to workgroups: `groups` sets of
+// parts (masks), in spans of `span` consecutive tiles; inside a span all
+// tiles of the first set, then of the next.  Unit u is one tile's set.
+struct Split {
+    uint32_t groups;
+    uint32_t span;
+    uint32_t mask[6];
+};
+
+struct Unit {
+    uint32_t tile;
+    uint32_t mask;
+};
+
+// Every value is uniform over the workgroup; the divisions run on the vector
+// unit, and readfirstlane brings what they give back to scalar registers, so
+// that the tests of the mask stay scalar branches.
+__device__ __forceinline__ Unit unit_of(const Split &sp, uint32_t ntiles, uint32_t u)
+{
+    if (sp.groups == 1) return {u, sp.mask[0]};
+    const uint32_t in_span = sp.span * sp.groups;
+    const uint32_t first = __builtin_amdgcn_readfirstlane(u / in_span) * sp.span;
+    const uint32_t r = u - first * sp.groups;
+    const uint32_t tiles = ntiles - first < sp.span ? ntiles - first : sp.span;
+    const uint32_t k = __builtin_amdgcn_readfirstlane(r / tiles);
+    return {first + (r - k * tiles), sp.mask[k]};
 }
 
 // Y = L_dir(U) X, or R_dir(U) X with kFlagRight: in0 = U, in1 = X, out0 = Y.

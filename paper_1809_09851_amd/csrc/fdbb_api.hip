@@ -316,7 +316,7 @@ const void *kernel_for(int op, int dim, int dtype, int ppt, bool nt)
     case kFamViscous: return kernel_pointwise(fam, dim, dtype, ppt, nt);
     case kFamCons2Char:
     case kFamChar2Cons: return kernel_char(fam, dim, dtype, ppt, nt);
-    case kFamFused: return kernel_fused(dim, dtype, ppt, nt);
+    case kFamFused: return kernel_fused(dim, dtype, ppt, nt, op == FDBB_OP_FUSED);
     case kFamAdjoint: return kernel_adjoint(dim, dtype, ppt, nt);
     case kFamEigen:
     case kFamCharApply: return kernel_eigen(fam, dim, dtype, ppt, nt);
@@ -334,7 +334,7 @@ size_t lds_bytes(int op, int dim, int dtype, int block, int ppt)
     return (size_t)block * ppt * K * K * elem_size(dtype);
 }
 
-// Values one point writes (every output of the op).
+// Values one point writes (every output of a pointwise op).
 int written_values(int op, int dim)
 {
     const int K = dim + 2;
@@ -349,35 +349,129 @@ int written_values(int op, int dim)
     }
 }
 
-// Waves of a pointwise kernel that may be resident on a compute unit.  A
-// wave writes as many rows as its op has output fields, far apart in memory,
-// so every resident wave adds that many open DRAM rows; past about 57 KB of
-// output in flight per compute unit (900 B per lane) more waves only make
-// the rows of different fields displace each other.  3D flux FP64 (120 B
-// written per point) at 12 000 017 points: 8 waves 301 us, 16 waves 316,
-// unlimited (32) 353; 2D flux FP64 (64 B): 10 waves 178, unlimited 200;
-// 3D Riemann invariants FP64 (56 B): 12-16 waves 1 % off the best, unlimited
-// 6 %.  Below 8 waves the loads of the next waves no longer cover the
-// latency (3D flux FP64 at 6 waves: 310 us; 1D flux FP32 at 8: 2.4 times
-// slower), and ops that write 32 B or less keep every wave.
+// How a call's output is dealt to workgroups (see Split), and what a
+// workgroup writes.
+struct SplitPlan {
+    Split dev{1, 1, {}};
+    bool blocks = false;  // K x K blocks are staged in LDS
+    bool split = false;   // one set of parts per workgroup
+    bool cached = false;  // the output fits in the last-level cache
+    int written = 0;      // bytes one point writes in the widest set of parts
+};
+
+// The ways of dealing, timed on the same buffers (3D unless noted; time over
+// that of one workgroup per tile, every part of it, at its best shape):
+//   kByDirection (FP64): 0.87 at 1 000 003 points, 0.95 from 4 M to 2^24;
+//     rows apart 0.88 / 0.96, so the state is read three times, not four;
+//   kFieldsApart (FP32): 0.95 at 1 000 003 points, 0.84 at 4 M, 0.85 at 12 M,
+//     by direction 0.96 / 0.88 / 0.88; beyond 4 GiB of blocks every split
+//     loses (1.02-1.3 at 2^24 and 25 M), and the whole tile is taken;
+//   1D and 2D (K*K a power of two or 9): the whole tile, a split gained
+//     nothing (2D FP64 0.92 against 0.93, 2D FP32 1.02 against 1.00);
+//   blocks that fit in the 256 MB last-level cache: the whole tile (200 003
+//     points FP32 split 1.12, FP64 0.96).
+// Spans of 131072 points: 32768 is level in FP64 (0.933 against 0.930 over 16
+// buffers), 10-20 % slower in FP32; one span over the whole call reads the
+// state from HBM again (2^24 FP64: 1.05).
+constexpr int64_t kSpanPoints = 131072;
+constexpr int64_t kApartMaxBytes = (int64_t)4 << 30;
+constexpr int64_t kLastLevelBytes = (int64_t)256 << 20;
+enum { kWhole = 0, kByDirection = 1, kFieldsApart = 2 };
+
+SplitPlan split_of(const Call &c, int64_t tile_pts)
+{
+    const int D = c.dim, K = D + 2;
+    const int es = (int)elem_size(c.dtype);
+    SplitPlan p;
+    Split &sp = p.dev;
+    sp.span = (uint32_t)std::max<int64_t>(1, kSpanPoints / tile_pts);
+    const auto add = [&](uint32_t mask, int values) {
+        sp.mask[sp.groups++] = mask;
+        p.written = std::max(p.written, values * es);
+    };
+    int mode = D < 3 ? kWhole : c.dtype == FDBB_F64 ? kByDirection : kFieldsApart;
+    if (D == 3 && family_of(c.op) == kFamFused && c.dtype == FDBB_F32 && (int64_t)D * K * K * es * c.a.n > kApartMaxBytes)
+        mode = kWhole;
+    const int64_t block_bytes = (int64_t)(c.op == FDBB_OP_EIGENVECTORS ? 2 : 1) * D * K * K * es * c.a.n;
+    p.cached = block_bytes <= kLastLevelBytes;
+    if (p.cached) mode = kWhole;
+    p.split = mode != kWhole;
+    if (c.op == FDBB_OP_EIGENVECTORS) {
+        sp.groups = 0;
+        p.blocks = true;
+        uint32_t all = 0;
+        for (int k = 0; k < 2 * D; ++k)
+            if ((k & 1) ? c.a.out1 != nullptr : c.a.out0 != nullptr) all |= 1u << k;
+        if (mode == kWhole) add(all, K * K * __builtin_popcount(all));
+        else
+            for (int k = 0; k < 2 * D; ++k)
+                if (all >> k & 1u) add(1u << k, K * K);
+    } else if (family_of(c.op) == kFamFused) {
+        sp.groups = 0;
+        p.blocks = c.a.out1 != nullptr;
+        const int rows = (c.a.out0 ? K * D : 0) + (c.a.out2 ? 2 * D + 1 : 0);
+        const uint32_t dirs = (1u << D) - 1u;
+        if (mode == kWhole || !p.blocks) {
+            add(dirs << kPartFields | dirs, rows + (p.blocks ? D * K * K : 0));
+        } else if (mode == kFieldsApart) {
+            if (rows) add(dirs << kPartFields, rows);
+            for (int d = 0; d < D; ++d) add(1u << d, K * K);
+        } else {
+            for (int d = 0; d < D; ++d) add(1u << d | 1u << (kPartFields + d), K * K + (rows + D - 1) / D);
+        }
+    } else {
+        p.written = written_values(c.op, D) * es;
+    }
+    return p;
+}
+
+// Waves that may be resident on a compute unit.  A wave writes as many rows
+// as its op has output fields, far apart in memory, so every resident wave
+// adds that many open DRAM rows; past about 57 KB of output in flight per
+// compute unit (900 B per lane) more waves only make the rows of different
+// fields displace each other.  3D flux FP64 (120 B written per point) at
+// 12 000 017 points: 8 waves 301 us, 16 waves 316, unlimited (32) 353; 2D
+// flux FP64 (64 B): 10 waves 178, unlimited 200; 3D Riemann invariants FP64
+// (56 B): 12-16 waves 1 % off the best, unlimited 6 %.  Below 8 waves the
+// loads of the next waves no longer cover the latency (3D flux FP64 at 6
+// waves: 310 us; 1D flux FP32 at 8: 2.4 times slower), and ops that write
+// 32 B or less keep every wave.
+//
+// Kernels that stage blocks take 1536 B per lane of a split set: 4 waves of
+// 256-thread workgroups in 3D FP64 (fused pass at 12 000 017 points: 4 waves
+// 0.95 of the unsplit time, 8 waves 1.01, 12 waves 1.05), 12 in FP32 (0.85;
+// 8 waves 0.89, 24 waves 0.99).  A whole tile at one point per thread takes
+// 3072 B in 2D FP64 (fused pass 8 waves 0.93, 16 waves 1.00), 2048 B in 1D
+// FP64 (16 waves 0.95, 24 waves 0.97, 12 waves 1.01) and 6208 B in FP32 (3D
+// beyond 4 GiB: 16 waves 0.95); more points per thread keep what their LDS
+// leaves, and so do blocks that stay in the last-level cache.
 constexpr int kMaxWaves = 32, kMinWaves = 8;
 constexpr int kWrittenPerLane = 900;
 
-int resident_waves(int op, int dim, int dtype, int ppt)
+int resident_waves(const SplitPlan &p, int dim, int dtype, int ppt)
 {
-    const int per_lane = written_values(op, dim) * (int)elem_size(dtype) * ppt;
+    if (p.blocks) {
+        int per_lane = 1536;
+        if (!p.split) {
+            if (ppt > 1 || p.cached) return kMaxWaves;
+            per_lane = dtype == FDBB_F32 ? 6208 : dim == 1 ? 2048 : 3072;
+        }
+        const int waves = std::max(1, per_lane / (p.written * ppt));
+        return std::min(kMaxWaves, waves);
+    }
+    const int per_lane = p.written * ppt;
     const int waves = std::max(kMinWaves / ppt, (kWrittenPerLane + per_lane / 2) / per_lane);
     return waves >= kMaxWaves - 4 ? kMaxWaves : std::max(1, waves);
 }
 
-// Dynamic LDS that keeps at most `waves` waves in workgroups of `block`
-// threads resident on a compute unit (0: no limit): the kernel does not
-// touch it, it only takes the space of the workgroups that should wait.
+// Dynamic LDS that keeps at most about `waves` waves in workgroups of
+// `block` threads resident on a compute unit (0: no limit): the kernel need
+// not touch it, it takes the space of the workgroups that should wait.
 // Allocations are made in steps of 1280 bytes.
-size_t residency_lds(int waves, int block, const DeviceInfo &dev)
+size_t residency_lds(int waves, int block, bool blocks, const DeviceInfo &dev)
 {
     if (waves >= kMaxWaves) return 0;
-    const int groups = std::max(1, (waves * 64 + block / 2) / block);
+    const int groups = std::max(1, (waves * 64 + (blocks ? 0 : block / 2)) / block);
     return dev.lds_max / groups / 1280 * 1280;
 }
 
@@ -422,25 +516,22 @@ int launch(Call &c, void *stream)
     DeviceInfo dev;
     rc = device_info(&dev);
     if (rc) return rc;
-    const bool needs_lds = (c.op == FDBB_OP_FLUX_JACOBIAN) || (c.op == FDBB_OP_FUSED && c.a.out1) ||
-                           (c.op == FDBB_OP_EIGENVECTORS);
-    size_t lds = 0;
-    if (needs_lds) lds = lds_bytes(c.op, c.dim, c.dtype, cfg.block, cfg.ppt);
-    else if (!stages_blocks(c.op))
-        lds = residency_lds(resident_waves(c.op, c.dim, c.dtype, cfg.ppt), cfg.block, dev);
+    const int64_t tile_pts = (int64_t)cfg.block * cfg.ppt;
+    int64_t ntiles = (c.a.n + tile_pts - 1) / tile_pts;
+    SplitPlan sp = split_of(c, tile_pts);
+    size_t lds = sp.blocks ? lds_bytes(c.op, c.dim, c.dtype, cfg.block, cfg.ppt) : 0;
+    lds = std::max(lds, residency_lds(resident_waves(sp, c.dim, c.dtype, cfg.ppt), cfg.block, sp.blocks, dev));
     rc = set_lds_attr(fn, lds, dev);
     if (rc) return rc;
 
-    const int64_t tile_pts = (int64_t)cfg.block * cfg.ppt;
-    int64_t ntiles = (c.a.n + tile_pts - 1) / tile_pts;
-    int64_t grid = ntiles;
+    int64_t grid = ntiles * sp.dev.groups;
     if (cfg.grid_cap > 0 && grid > cfg.grid_cap) grid = cfg.grid_cap;
     // keep a dispatch below 2^31 work-items (the grid-dimension bound HIP
     // reports on this device); the kernels loop over tiles, so a capped grid
     // still covers every point
     const int64_t max_grid = 0x7fffffffLL / cfg.block;
     if (grid > max_grid) grid = max_grid;
-    void *args[] = {&c.a, &ntiles};
+    void *args[] = {&c.a, &ntiles, &sp.dev};
     hipError_t e = hipLaunchKernel(fn, dim3((unsigned)grid), dim3((unsigned)cfg.block), args, lds,
                                    (hipStream_t)stream);
     if (e != hipSuccess) return fail_hip(e, "kernel launch");

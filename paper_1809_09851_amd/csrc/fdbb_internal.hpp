@@ -47,11 +47,12 @@ enum Family : int {
     kNumFamilies
 };
 
-// Single-operation kernels: void k(Args a, int64_t ntiles).  nt selects
+// Single-operation kernels: void k(Args a, int64_t ntiles), and a third
+// argument Split for the fused pass and the eigenvector blocks.  nt selects
 // non-temporal output stores.
 const void *kernel_pointwise(int family, int dim, int dtype, int ppt, bool nt);
 const void *kernel_char(int family, int dim, int dtype, int ppt, bool nt);
-const void *kernel_fused(int dim, int dtype, int ppt, bool nt);
+const void *kernel_fused(int dim, int dtype, int ppt, bool nt, bool rows);  // rows: flux or invariants too
 const void *kernel_adjoint(int dim, int dtype, int ppt, bool nt);
 const void *kernel_eigen(int family, int dim, int dtype, int ppt, bool nt);
 

@@ -23,7 +23,7 @@ __device__ __forceinline__ void run_tile(int op, const Args &a, int64_t tile0, u
     case 3:
     case 16: tile_flux<D, T, P, NT>(a, tile0); break;
     case 4:
-    case 8: tile_fused<D, T, P, NT>(a, tile0, reinterpret_cast<T *>(smem)); break;
+    case 8: tile_fused<D, T, P, NT>(a, tile0, ~0u, reinterpret_cast<T *>(smem)); break;
     case 5: tile_riemann<D, T, P, NT>(a, tile0); break;
     case 6: tile_cons2char<D, T, P, NT>(a, tile0); break;
     case 7: tile_char2cons<D, T, P, NT>(a, tile0); break;
