@@ -13,7 +13,7 @@ def _as_fields(g: torch.Tensor) -> torch.Tensor:
     a field set with unit point stride."""
     if g.dim() == 2 and (g.shape[1] <= 1 or g.stride(1) == 1) and g.stride(0) >= g.shape[1]:
         return g
-    return F.to_fields(g.contiguous())
+    return F.to_fields(g)
 
 
 class EulerFlux(torch.autograd.Function):

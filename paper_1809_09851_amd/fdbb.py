@@ -2,7 +2,9 @@
 
 Argument marshalling only: every building block runs in the HIP kernels of
 the library.  There is no CPU fallback; if the library is missing, loading
-raises.
+raises.  Calls on plain device tensors are marshalled by the extension module
+``_binding`` (csrc/binding.cpp), which answers None for everything else; the
+code here then makes the call, or raises what is wrong with it.
 
 Field sets are 2-D tensors ``(fields, n)`` whose rows are ``ld`` elements
 apart (``ld = t.stride(0) >= n``, unit stride along points), float64 or
@@ -72,6 +74,32 @@ class ServerStats(ctypes.Structure):
 _lib = None
 
 
+def _first(name):
+    """Stand-in for a function of the extension module until the library is
+    loaded, which puts the function itself in its place."""
+    def call(*args):
+        library()
+        return globals()[name](*args)
+    return call
+
+
+_run, _char_apply, _viscous_flux = _first("_run"), _first("_char_apply"), _first("_viscous_flux")
+_empty_fields, _empty_blocks = _first("_empty_fields"), _first("_empty_blocks")
+BLOCKS, FLAT = -1, -2  # how a slot of _run lies, next to a number of field rows
+
+
+def _bind(lib):
+    global _run, _char_apply, _viscous_flux, _empty_fields, _empty_blocks
+    try:
+        from . import _binding
+    except ImportError as exc:
+        raise RuntimeError("the native binding is not built; run `python -m paper_1809_09851_amd.build`") from exc
+    addr = [ctypes.cast(getattr(lib, f), _p).value for f in ("fdbb_task_run", "fdbb_char_apply", "fdbb_viscous_flux")]
+    _binding.bind(*addr, torch._C._cuda_getCurrentRawStream)
+    _run, _char_apply, _viscous_flux = _binding.run, _binding.char_apply, _binding.viscous_flux
+    _empty_fields, _empty_blocks = _binding.empty_fields, _binding.empty_blocks
+
+
 def library():
     """Load libfdbb.so (built by ``python -m paper_1809_09851_amd.build``)."""
     global _lib
@@ -132,6 +160,7 @@ def library():
         lib.fdbb_probe_read.argtypes = [_p, _i64, _p, _i, _p]
         lib.fdbb_probe_fused_stores.argtypes = [_p, _p, _p, _i64, _p]
         lib.fdbb_probe_pow.argtypes = [_p, _p, _p, _i64, _i, _p]
+        _bind(lib)
         _lib = lib
         if os.environ.get("FDBB_NO_TUNED_TABLE") != "1":
             from . import tune
@@ -157,7 +186,7 @@ def dtype_code(t: torch.dtype) -> int:
 
 def _stream(stream):
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
     return int(stream)
@@ -219,6 +248,17 @@ def to_fields(x: torch.Tensor) -> torch.Tensor:
     return out
 
 
+def _fields_like(fields: int, U: torch.Tensor) -> torch.Tensor:
+    """empty_fields for U's points, type and device."""
+    t = _empty_fields(fields, U)
+    return empty_fields(fields, U.shape[1], U.dtype, U.device) if t is None else t
+
+
+def _blocks_like(dim: int, U: torch.Tensor) -> torch.Tensor:
+    t = _empty_blocks(dim, U)
+    return empty_blocks(dim, U.shape[1], U.dtype, U.device) if t is None else t
+
+
 def _dim_of(U: torch.Tensor) -> int:
     dim = U.shape[0] - 2
     if dim not in (1, 2, 3):
@@ -228,6 +268,10 @@ def _dim_of(U: torch.Tensor) -> int:
 
 # ------------------------------------------------------------ C mirrors
 def fdbb_cons2prim(dim, gamma, U, V, n=None, stream=None):
+    rc = _run(0, dim, 0, gamma, n, stream if stream is None else _stream(stream),
+              U, dim + 2, None, 0, V, dim + 2, None, 0, None, 0)
+    if rc is not None:
+        return check(rc) if rc else None
     u, ldu = _fields(U, dim + 2, "U")
     v, ldv = _fields(V, dim + 2, "V")
     n = U.shape[1] if n is None else n
@@ -235,6 +279,10 @@ def fdbb_cons2prim(dim, gamma, U, V, n=None, stream=None):
 
 
 def fdbb_prim2cons(dim, gamma, V, U, n=None, stream=None):
+    rc = _run(1, dim, 0, gamma, n, stream if stream is None else _stream(stream),
+              V, dim + 2, None, 0, U, dim + 2, None, 0, None, 0)
+    if rc is not None:
+        return check(rc) if rc else None
     v, ldv = _fields(V, dim + 2, "V")
     u, ldu = _fields(U, dim + 2, "U")
     n = V.shape[1] if n is None else n
@@ -252,6 +300,10 @@ def fdbb_velocity_magnitude2(dim, U, y, n=None, stream=None):
 
 
 def fdbb_eos(dim, gamma, U, p=None, c=None, n=None, stream=None):
+    rc = _run(2, dim, 0, gamma, n, stream if stream is None else _stream(stream),
+              U, dim + 2, None, 0, p, 0 if p is None else FLAT, c, 0 if c is None else FLAT, None, 0)
+    if rc is not None:
+        return check(rc) if rc else None
     u, ldu = _fields(U, dim + 2, "U")
     n = U.shape[1] if n is None else n
     check(library().fdbb_eos(dim, gamma, dtype_code(U.dtype), u, ldu, _ptr(p), _ptr(c), n,
@@ -259,6 +311,10 @@ def fdbb_eos(dim, gamma, U, p=None, c=None, n=None, stream=None):
 
 
 def fdbb_flux(dim, gamma, U, F, n=None, stream=None):
+    rc = _run(3, dim, 0, gamma, n, stream if stream is None else _stream(stream),
+              U, dim + 2, None, 0, F, (dim + 2) * dim, None, 0, None, 0)
+    if rc is not None:
+        return check(rc) if rc else None
     u, ldu = _fields(U, dim + 2, "U")
     f, ldf = _fields(F, (dim + 2) * dim, "F")
     n = U.shape[1] if n is None else n
@@ -266,6 +322,10 @@ def fdbb_flux(dim, gamma, U, F, n=None, stream=None):
 
 
 def fdbb_flux_direction(dim, direction, gamma, U, Fd, n=None, stream=None):
+    rc = _run(16, dim, direction, gamma, n, stream if stream is None else _stream(stream),
+              U, dim + 2, None, 0, Fd, dim + 2, None, 0, None, 0)
+    if rc is not None:
+        return check(rc) if rc else None
     u, ldu = _fields(U, dim + 2, "U")
     f, ldf = _fields(Fd, dim + 2, "Fd")
     n = U.shape[1] if n is None else n
@@ -274,6 +334,10 @@ def fdbb_flux_direction(dim, direction, gamma, U, Fd, n=None, stream=None):
 
 
 def fdbb_flux_jacobian(dim, gamma, U, A, n=None, stream=None):
+    rc = _run(4, dim, 0, gamma, n, stream if stream is None else _stream(stream),
+              U, dim + 2, None, 0, A, BLOCKS, None, 0, None, 0)
+    if rc is not None:
+        return check(rc) if rc else None
     u, ldu = _fields(U, dim + 2, "U")
     a, lda = _blocks(A, dim)
     n = U.shape[1] if n is None else n
@@ -282,6 +346,10 @@ def fdbb_flux_jacobian(dim, gamma, U, A, n=None, stream=None):
 
 
 def fdbb_riemann_invariants(dim, gamma, U, R, n=None, stream=None):
+    rc = _run(5, dim, 0, gamma, n, stream if stream is None else _stream(stream),
+              U, dim + 2, None, 0, R, 2 * dim + 1, None, 0, None, 0)
+    if rc is not None:
+        return check(rc) if rc else None
     u, ldu = _fields(U, dim + 2, "U")
     r, ldr = _fields(R, 2 * dim + 1, "R")
     n = U.shape[1] if n is None else n
@@ -290,6 +358,10 @@ def fdbb_riemann_invariants(dim, gamma, U, R, n=None, stream=None):
 
 
 def fdbb_cons2char(dim, direction, gamma, U, W, n=None, stream=None):
+    rc = _run(6, dim, direction, gamma, n, stream if stream is None else _stream(stream),
+              U, dim + 2, None, 0, W, dim + 2, None, 0, None, 0)
+    if rc is not None:
+        return check(rc) if rc else None
     u, ldu = _fields(U, dim + 2, "U")
     w, ldw = _fields(W, dim + 2, "W")
     n = U.shape[1] if n is None else n
@@ -298,6 +370,10 @@ def fdbb_cons2char(dim, direction, gamma, U, W, n=None, stream=None):
 
 
 def fdbb_char2cons(dim, direction, gamma, W, U, n=None, stream=None):
+    rc = _run(7, dim, direction, gamma, n, stream if stream is None else _stream(stream),
+              W, dim + 2, None, 0, U, dim + 2, None, 0, None, 0)
+    if rc is not None:
+        return check(rc) if rc else None
     w, ldw = _fields(W, dim + 2, "W")
     u, ldu = _fields(U, dim + 2, "U")
     n = W.shape[1] if n is None else n
@@ -306,6 +382,10 @@ def fdbb_char2cons(dim, direction, gamma, W, U, n=None, stream=None):
 
 
 def fdbb_euler_fused(dim, gamma, U, F=None, A=None, R=None, n=None, stream=None):
+    rc = _run(8, dim, 0, gamma, n, stream if stream is None else _stream(stream),
+              U, dim + 2, None, 0, F, 0 if F is None else (dim + 2) * dim, A, 0 if A is None else BLOCKS, R, 0 if R is None else 2 * dim + 1)
+    if rc is not None:
+        return check(rc) if rc else None
     u, ldu = _fields(U, dim + 2, "U")
     f, ldf = _fields(F, (dim + 2) * dim, "F") if F is not None else (None, 0)
     a, lda = _blocks(A, dim) if A is not None else (None, 0)
@@ -316,6 +396,10 @@ def fdbb_euler_fused(dim, gamma, U, F=None, A=None, R=None, n=None, stream=None)
 
 
 def fdbb_flux_adjoint(dim, direction, gamma, U, Fbar, Ubar, n=None, stream=None):
+    rc = _run(9, dim, direction, gamma, n, stream if stream is None else _stream(stream),
+              U, dim + 2, Fbar, (dim + 2) * dim if direction < 0 else dim + 2, Ubar, dim + 2, None, 0, None, 0)
+    if rc is not None:
+        return check(rc) if rc else None
     u, ldu = _fields(U, dim + 2, "U")
     fb, ldfb = _fields(Fbar, (dim + 2) * dim if direction < 0 else dim + 2, "Fbar")
     ub, ldub = _fields(Ubar, dim + 2, "Ubar")
@@ -325,6 +409,10 @@ def fdbb_flux_adjoint(dim, direction, gamma, U, Fbar, Ubar, n=None, stream=None)
 
 
 def fdbb_eigenvectors(dim, gamma, U, L=None, R=None, n=None, stream=None):
+    rc = _run(11, dim, 0, gamma, n, stream if stream is None else _stream(stream),
+              U, dim + 2, None, 0, L, 0 if L is None else BLOCKS, R, 0 if R is None else BLOCKS, None, 0)
+    if rc is not None:
+        return check(rc) if rc else None
     u, ldu = _fields(U, dim + 2, "U")
     lp, ldl = _blocks(L, dim, "L") if L is not None else (None, 0)
     rp, ldr = _blocks(R, dim, "R") if R is not None else (None, 0)
@@ -334,6 +422,9 @@ def fdbb_eigenvectors(dim, gamma, U, L=None, R=None, n=None, stream=None):
 
 
 def fdbb_char_apply(dim, direction, mode, gamma, U, X, Y, n=None, stream=None):
+    rc = _char_apply(dim, direction, mode, gamma, n, stream if stream is None else _stream(stream), U, X, Y)
+    if rc is not None:
+        return check(rc) if rc else None
     u, ldu = _fields(U, dim + 2, "U")
     x, ldx = _fields(X, dim + 2, "X")
     y, ldy = _fields(Y, dim + 2, "Y")
@@ -343,6 +434,10 @@ def fdbb_char_apply(dim, direction, mode, gamma, U, X, Y, n=None, stream=None):
 
 
 def fdbb_roe_average(dim, gamma, UL, UR, Uh, n=None, stream=None):
+    rc = _run(13, dim, 0, gamma, n, stream if stream is None else _stream(stream),
+              UL, dim + 2, UR, dim + 2, Uh, dim + 2, None, 0, None, 0)
+    if rc is not None:
+        return check(rc) if rc else None
     ul, ldl = _fields(UL, dim + 2, "UL")
     ur, ldr = _fields(UR, dim + 2, "UR")
     uh, ldh = _fields(Uh, dim + 2, "Uh")
@@ -364,6 +459,9 @@ def fdbb_eos_pvt(dim, eos, params, U, p=None, c=None, T=None, n=None, stream=Non
 
 
 def fdbb_viscous_flux(dim, mu, kappa, U, G, gradT, Fv, n=None, stream=None):
+    rc = _viscous_flux(dim, mu, kappa, n, stream if stream is None else _stream(stream), U, G, gradT, Fv)
+    if rc is not None:
+        return check(rc) if rc else None
     u, ldu = _fields(U, dim + 2, "U")
     g, ldg = _fields(G, dim * dim, "G")
     t, ldt = _fields(gradT, dim, "gradT")
@@ -453,14 +551,14 @@ def fdbb_version() -> int:
 # ------------------------------------------------------------ allocating helpers
 def cons2prim(U, gamma=1.4, stream=None):
     dim = _dim_of(U)
-    V = empty_fields(dim + 2, U.shape[1], U.dtype, U.device)
+    V = _fields_like(dim + 2, U)
     fdbb_cons2prim(dim, gamma, U, V, stream=stream)
     return V
 
 
 def prim2cons(V, gamma=1.4, stream=None):
     dim = _dim_of(V)
-    U = empty_fields(dim + 2, V.shape[1], V.dtype, V.device)
+    U = _fields_like(dim + 2, V)
     fdbb_prim2cons(dim, gamma, V, U, stream=stream)
     return U
 
@@ -486,55 +584,54 @@ def flux(U, gamma=1.4, stream=None, direction=None):
     """The flux tensor (K*D fields), or F_direction alone (K fields)."""
     dim = _dim_of(U)
     if direction is not None:
-        Fd = empty_fields(dim + 2, U.shape[1], U.dtype, U.device)
+        Fd = _fields_like(dim + 2, U)
         fdbb_flux_direction(dim, direction, gamma, U, Fd, stream=stream)
         return Fd
-    F = empty_fields((dim + 2) * dim, U.shape[1], U.dtype, U.device)
+    F = _fields_like((dim + 2) * dim, U)
     fdbb_flux(dim, gamma, U, F, stream=stream)
     return F
 
 
 def flux_jacobian(U, gamma=1.4, stream=None):
     dim = _dim_of(U)
-    A = empty_blocks(dim, U.shape[1], U.dtype, U.device)
+    A = _blocks_like(dim, U)
     fdbb_flux_jacobian(dim, gamma, U, A, stream=stream)
     return A
 
 
 def riemann_invariants(U, gamma=1.4, stream=None):
     dim = _dim_of(U)
-    R = empty_fields(2 * dim + 1, U.shape[1], U.dtype, U.device)
+    R = _fields_like(2 * dim + 1, U)
     fdbb_riemann_invariants(dim, gamma, U, R, stream=stream)
     return R
 
 
 def cons2char(U, direction, gamma=1.4, stream=None):
     dim = _dim_of(U)
-    W = empty_fields(dim + 2, U.shape[1], U.dtype, U.device)
+    W = _fields_like(dim + 2, U)
     fdbb_cons2char(dim, direction, gamma, U, W, stream=stream)
     return W
 
 
 def char2cons(W, direction, gamma=1.4, stream=None):
     dim = _dim_of(W)
-    U = empty_fields(dim + 2, W.shape[1], W.dtype, W.device)
+    U = _fields_like(dim + 2, W)
     fdbb_char2cons(dim, direction, gamma, W, U, stream=stream)
     return U
 
 
 def euler_fused(U, gamma=1.4, flux=True, jacobian=True, riemann=True, stream=None):
     dim = _dim_of(U)
-    n = U.shape[1]
-    F = empty_fields((dim + 2) * dim, n, U.dtype, U.device) if flux else None
-    A = empty_blocks(dim, n, U.dtype, U.device) if jacobian else None
-    R = empty_fields(2 * dim + 1, n, U.dtype, U.device) if riemann else None
+    F = _fields_like((dim + 2) * dim, U) if flux else None
+    A = _blocks_like(dim, U) if jacobian else None
+    R = _fields_like(2 * dim + 1, U) if riemann else None
     fdbb_euler_fused(dim, gamma, U, F, A, R, stream=stream)
     return F, A, R
 
 
 def flux_adjoint(U, Fbar, gamma=1.4, direction=-1, stream=None):
     dim = _dim_of(U)
-    Ub = empty_fields(dim + 2, U.shape[1], U.dtype, U.device)
+    Ub = _fields_like(dim + 2, U)
     fdbb_flux_adjoint(dim, direction, gamma, U, Fbar, Ub, stream=stream)
     return Ub
 
@@ -581,8 +678,8 @@ def probe_read(src: torch.Tensor, sink: torch.Tensor, grid: int = 0, stream=None
 def eigenvectors(U, gamma=1.4, left=True, right=True, stream=None):
     """(L, R) eigenvector blocks of every direction, (D, n, K, K) each."""
     dim = _dim_of(U)
-    L = empty_blocks(dim, U.shape[1], U.dtype, U.device) if left else None
-    R = empty_blocks(dim, U.shape[1], U.dtype, U.device) if right else None
+    L = _blocks_like(dim, U) if left else None
+    R = _blocks_like(dim, U) if right else None
     fdbb_eigenvectors(dim, gamma, U, L, R, stream=stream)
     return L, R
 
@@ -591,7 +688,7 @@ def viscous_flux(U, G, gradT, mu, kappa, stream=None):
     """Viscous flux tensor (K*D fields, flux tensor layout) of the state U
     with velocity gradient G (D*D fields) and temperature gradient gradT."""
     dim = _dim_of(U)
-    Fv = empty_fields((dim + 2) * dim, U.shape[1], U.dtype, U.device)
+    Fv = _fields_like((dim + 2) * dim, U)
     fdbb_viscous_flux(dim, mu, kappa, U, G, gradT, Fv, stream=stream)
     return Fv
 
@@ -607,7 +704,7 @@ def eos_pvt(U, eos="perfect_gas", params=(3.5, 2.5), stream=None):
 def roe_average(UL, UR, gamma=1.4, stream=None):
     """Roe-averaged conservative state between UL and UR."""
     dim = _dim_of(UL)
-    Uh = empty_fields(dim + 2, UL.shape[1], UL.dtype, UL.device)
+    Uh = _fields_like(dim + 2, UL)
     fdbb_roe_average(dim, gamma, UL, UR, Uh, stream=stream)
     return Uh
 
@@ -615,6 +712,6 @@ def roe_average(UL, UR, gamma=1.4, stream=None):
 def char_apply(U, X, direction, mode=0, gamma=1.4, stream=None):
     """L_dir(U) X (mode 0) or R_dir(U) X (mode 1)."""
     dim = _dim_of(U)
-    Y = empty_fields(dim + 2, U.shape[1], U.dtype, U.device)
+    Y = _fields_like(dim + 2, U)
     fdbb_char_apply(dim, direction, mode, gamma, U, X, Y, stream=stream)
     return Y
