@@ -321,14 +321,17 @@ typedef struct fdbb_batch_plan fdbb_batch_plan;
 
 /* Create a plan for up to `capacity` tasks (>= ntasks) and load `tasks`
  * into it.  Each task is validated as its single-call entry point would be.
- * The plan owns a device copy of the task table, the tile prefix sums and a
- * HIP graph holding one persistent kernel with `grid` workgroups of `block`
+ * The plan owns a device copy of the task table, the tile prefix sums and
+ * HIP graphs of one kernel with at most `grid` workgroups of `block`
  * threads (64..256 in multiples of 64; grid 0 picks one sized to the
  * device), `ppt` points per thread (1, 2, 4 or 8) and regular (0),
  * streaming (1: the nt bit) or streaming device-coherent (2: nt and sc1)
  * output stores.  block == 0 takes the batch configuration installed for
  * the first task's storage type (FDBB_F64 for an empty list; see
- * fdbb_set_batch_config) and ignores ppt, grid and nontemporal.  Tasks that
+ * fdbb_set_batch_config) and ignores ppt, grid and nontemporal; that
+ * configuration is meant for lists that all write blocks (fused passes and
+ * flux Jacobians of one dim and storage type), and other lists then run in a
+ * shape that suits them.  Tasks that
  * overlap one another's outputs are rejected (FDBB_EALIAS).  Jacobian
  * staging needs LDS; a plan holds what its first task list needs, or, when
  * created with ntasks == 0, what any task needs (later task lists needing
@@ -343,12 +346,13 @@ int fdbb_batch_plan_create(const fdbb_task *tasks, int ntasks, int capacity, int
 int fdbb_batch_plan_update(fdbb_batch_plan *plan, const fdbb_task *tasks, int ntasks,
                            void *stream);
 
-/* Run the plan's persistent launch on `stream`: use_graph != 0 replays the
- * captured HIP graph, 0 launches the same kernel directly.  The graph was
- * captured with the LDS the plan reserved at creation (a plan created empty
- * reserves 3D FP64 Jacobian staging, which leaves room for one or two
- * workgroups per compute unit); a direct launch takes only what the current
- * task list stages, none for a list without Jacobian blocks. */
+/* Run the plan's launch on `stream`.  use_graph != 0 replays the HIP graph
+ * captured at creation where the current task list wants the launch it holds
+ * (kernel, shape and LDS), and is a direct launch otherwise; 0 always launches
+ * directly.  While `stream` is being captured, and for good once a list was
+ * uploaded on a capturing stream, the launch is the general one in the shape
+ * the plan was created with, which stays right when the capturing graph is
+ * replayed over later lists. */
 int fdbb_batch_exec(fdbb_batch_plan *plan, void *stream, int use_graph);
 
 /* The batch configuration that plans created with block == 0, the

@@ -43,6 +43,7 @@ SOURCES = [
     "kernels_fused.hip",
     "kernels_adjoint.hip",
     "kernels_batch.hip",
+    "kernels_batch_fused.hip",
     "kernels_eigen.hip",
     "probes.hip",
     "fdbb_server.cpp",

@@ -946,21 +946,21 @@ struct Split {
 
 struct Unit {
     uint32_t tile;
-    uint32_t mask;
+    uint32_t set;
 };
 
 // Every value is uniform over the workgroup; the divisions run on the vector
 // unit, and readfirstlane brings what they give back to scalar registers, so
-// that the tests of the mask stay scalar branches.
-__device__ __forceinline__ Unit unit_of(const Split &sp, uint32_t ntiles, uint32_t u)
+// that the tests of a mask stay scalar branches.
+__device__ __forceinline__ Unit unit_of(uint32_t groups, uint32_t span, uint32_t ntiles, uint32_t u)
 {
-    if (sp.groups == 1) return {u, sp.mask[0]};
-    const uint32_t in_span = sp.span * sp.groups;
-    const uint32_t first = __builtin_amdgcn_readfirstlane(u / in_span) * sp.span;
-    const uint32_t r = u - first * sp.groups;
-    const uint32_t tiles = ntiles - first < sp.span ? ntiles - first : sp.span;
+    if (groups == 1) return {u, 0u};
+    const uint32_t in_span = span * groups;
+    const uint32_t first = __builtin_amdgcn_readfirstlane(u / in_span) * span;
+    const uint32_t r = u - first * groups;
+    const uint32_t tiles = ntiles - first < span ? ntiles - first : span;
     const uint32_t k = __builtin_amdgcn_readfirstlane(r / tiles);
-    return {first + (r - k * tiles), sp.mask[k]};
+    return {first + (r - k * tiles), k};
 }
 
 // Y = L_dir(U) X, or R_dir(U) X with kFlagRight: in0 = U, in1 = X, out0 = Y.

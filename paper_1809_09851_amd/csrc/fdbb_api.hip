@@ -373,7 +373,6 @@ struct SplitPlan {
 // Spans of 131072 points: 32768 is level in FP64 (0.933 against 0.930 over 16
 // buffers), 10-20 % slower in FP32; one span over the whole call reads the
 // state from HBM again (2^24 FP64: 1.05).
-constexpr int64_t kSpanPoints = 131072;
 constexpr int64_t kApartMaxBytes = (int64_t)4 << 30;
 constexpr int64_t kLastLevelBytes = (int64_t)256 << 20;
 enum { kWhole = 0, kByDirection = 1, kFieldsApart = 2 };
@@ -1029,32 +1028,160 @@ static int64_t *table_header(unsigned char *base) { return reinterpret_cast<int6
 static int64_t *table_prefix(unsigned char *base) { return reinterpret_cast<int64_t *>(base) + 2; }
 static TaskDev *table_tasks(unsigned char *base, int cap) { return reinterpret_cast<TaskDev *>(base + table_task_offset(cap)); }
 
+// What a batch launches with.
+struct BatchLaunch {
+    const void *kernel = nullptr;
+    int block = 256;
+    int ppt = 1;
+    int nt = 1;
+    int grid = 0;
+    size_t lds = 0;      // dynamic LDS: what the list stages, or more to bound residency
+    bool parts = false;  // a tile's parts are dealt to several units
+
+    bool operator==(const BatchLaunch &o) const
+    {
+        return kernel == o.kernel && block == o.block && grid == o.grid && lds == o.lds;
+    }
+};
+
+// The plan's table: the layout above with its prefix sums in tiles of the
+// creation shape, which the general launch reads, behind a second header and
+// second prefix sums (cap + 1) in units of the current list's own launch.
 struct fdbb_batch_plan {
     int device = 0;
     int capacity = 0;
     int ntasks = 0;
-    int block = 256;
-    int ppt = 1;
-    int grid = 0;
-    int nt = 1;
-    size_t lds = 0;      // reserved at creation: what the captured graph launches with
-    size_t cur_lds = 0;  // what the current task list needs: direct launches use it
+    bool installed = false;     // block == 0 at creation: the installed configurations
+    bool general_only = false;  // a list was uploaded inside a capture (see fdbb_batch_plan_update)
+    BatchLaunch base;           // as created; base.lds is the staging a task list may need
+    BatchLaunch cur;            // the current task list's own launch
+    BatchLaunch captured;       // what `exec` launches with
+    size_t list_lds = 0;        // staging of the current task list in the creation shape
     int64_t points = 0;
-    int64_t tiles = 0;
-    const void *kernel = nullptr;
-    unsigned char *dev = nullptr;   // task table (layout above), capacity `capacity`
+    int64_t tiles = 0;          // of the creation shape
+    unsigned char *dev = nullptr;   // task table, capacity `capacity`
     unsigned char *host = nullptr;  // pinned staging copy of the same layout
     size_t bytes = 0;
     hipEvent_t uploaded = nullptr;  // the last upload has left the staging copy
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
+    hipGraphExec_t general = nullptr;  // the general launch in the creation shape
+    hipGraphExec_t exec = nullptr;     // the first list's own launch, if another
 
-    int64_t *header(unsigned char *base) const { return table_header(base); }
-    int64_t *prefix(unsigned char *base) const { return table_prefix(base); }
-    TaskDev *tasks(unsigned char *base) const { return table_tasks(base, capacity); }
+    size_t units_bytes() const { return ((2 + (size_t)capacity + 1) * sizeof(int64_t) + 63) & ~(size_t)63; }
+    int64_t *unit_header(unsigned char *t) const { return reinterpret_cast<int64_t *>(t); }
+    int64_t *unit_prefix(unsigned char *t) const { return reinterpret_cast<int64_t *>(t) + 2; }
+    unsigned char *table(unsigned char *t) const { return t + units_bytes(); }
 };
 
 namespace {
+
+// Whether a task writes K x K blocks.
+bool writes_blocks(const fdbb_task &t) { return t.op == FDBB_OP_FLUX_JACOBIAN || (t.op == FDBB_OP_FUSED && t.out1); }
+
+// Sets of parts a block-writing 3D task's tiles are dealt in when they are
+// dealt apart, as split_of deals a single call's.
+int task_groups(const fdbb_task &t)
+{
+    const bool rows = t.op == FDBB_OP_FUSED && (t.out0 || t.out2);
+    return t.dtype == FDBB_F32 && rows ? t.dim + 1 : t.dim;
+}
+
+// Kernel and shape of a task list (valid tasks), timed against one workgroup
+// per tile and the general kernel, on the same buffers.
+//
+// A list of block-writing tasks of one dim and storage type takes the fused
+// batch kernel in the plan's shape (time over the general kernel's at its
+// best shape):
+//   3D FP64, parts by direction, 8 waves: 0.89 at 14 M points in 96 tasks,
+//     0.92 at 3 M in 40 (whole tile, 4 waves: 0.95 and 0.94; parts at 4
+//     waves 1.09, 6 waves 1.1, unlimited 0.97); from 32 GiB of blocks the
+//     whole tile at 4 waves wins (72.8 M in 512 tasks 0.97, by parts 1.01;
+//     55 M 0.96 and 0.96; 40 M 0.96 and 0.88);
+//   3D FP32, parts, no bound: 0.92 / 0.73; 8 waves 1.2, and beyond 4 GiB the
+//     whole tile at 16 waves as in a single call (25 M 0.95, 18 M 0.99, by
+//     parts 1.12 and 1.04);
+//   2D whole tile: FP64 8 waves 0.95 (unlimited 1.03), FP32 0.72; 1D 0.78
+//     and 0.53 without a bound (16 waves 0.78 and 0.76);
+//   lists that fit in the last-level cache: the whole tile, no bound and, in
+//     2D and 3D, regular stores under the installed configurations (3D FP64
+//     200 K points 0.93, streaming 1.02; 1D 900 K 0.92 streaming, 1.03
+//     regular).
+// Any other list under the installed configurations takes the general kernel
+// at 128 threads and, unless its grid is smaller, a workgroup per tile: one
+// point per thread where it stages 2D or 3D blocks (48 mixed requests of
+// 733 MB: 0.75 of the fused shape's time; 2 points 0.81), else two (1D and
+// 3D flux FP64 0.92 and 0.84; 1 point 1.3 and 0.90).
+constexpr int64_t kListApartMaxBytes = (int64_t)32 << 30;
+
+BatchLaunch pick_launch(const fdbb_task *tasks, int ntasks, const BatchLaunch &base, bool installed,
+                        const DeviceInfo &dev)
+{
+    BatchLaunch l = base;
+    const fdbb_task *first = nullptr;
+    bool uniform = true;
+    int rows = 0;
+    int64_t points = 0;
+    for (int b = 0; b < ntasks; ++b) {
+        const fdbb_task &t = tasks[b];
+        if (t.n == 0) continue;
+        if (!first) first = &t;
+        uniform = writes_blocks(t) && t.dim == first->dim && t.dtype == first->dtype;
+        if (!uniform) break;
+        if (t.op == FDBB_OP_FUSED)
+            rows = std::max(rows, (t.out0 ? (t.dim + 2) * t.dim : 0) + (t.out2 ? 2 * t.dim + 1 : 0));
+        points += t.n;
+    }
+    if (!first) return l;
+    if (uniform) {
+        const int D = first->dim, KK = (D + 2) * (D + 2), es = (int)elem_size(first->dtype);
+        const void *k = kernel_batch_fused(D, first->dtype, base.ppt, base.nt);
+        if (k) {
+            const bool f64 = first->dtype == FDBB_F64;
+            const int64_t block_bytes = (int64_t)D * KK * es * points;
+            const bool cached = block_bytes + (int64_t)rows * es * points <= kLastLevelBytes;
+            l.parts = D == 3 && !cached && block_bytes <= (f64 ? kListApartMaxBytes : kApartMaxBytes);
+            const int written = es * l.ppt * (!l.parts ? rows + D * KK : f64 ? KK + (rows + D - 1) / D : KK);
+            int per_lane = 0;  // bytes that the resident waves write per lane, 0: no bound
+            if (l.parts) per_lane = f64 ? 2200 : 0;
+            else if (!cached && D > 1 && l.ppt == 1) per_lane = f64 ? 3072 : 6208;
+            const int waves = per_lane ? std::max(1, std::min(kMaxWaves, per_lane / written)) : kMaxWaves;
+            if (installed && cached && D > 1) l.nt = 0, k = kernel_batch_fused(D, first->dtype, l.ppt, l.nt);
+            l.kernel = k;
+            l.lds = std::max(lds_bytes(FDBB_OP_FLUX_JACOBIAN, D, first->dtype, l.block, l.ppt),
+                             residency_lds(waves, l.block, true, dev));
+            return l;
+        }
+    }
+    if (installed) {
+        bool staged = false;
+        for (int b = 0; b < ntasks; ++b) staged = staged || (writes_blocks(tasks[b]) && tasks[b].dim > 1);
+        l.block = 128, l.ppt = staged ? 1 : 2, l.nt = staged ? 2 : 1;
+        l.grid = dev.cus * 64;
+        l.kernel = kernel_batch(l.ppt, l.nt);
+    }
+    l.lds = 0;
+    for (int b = 0; b < ntasks; ++b)
+        if (writes_blocks(tasks[b]))
+            l.lds = std::max(l.lds, lds_bytes(tasks[b].op, tasks[b].dim, tasks[b].dtype, l.block, l.ppt));
+    return l;
+}
+
+// The units of the launch `l` over `ntasks` tasks: fills the second header
+// and prefix sums and each task's part of them, and cuts the grid to the
+// units there are.
+void fill_units(int ntasks, BatchLaunch &l, int64_t *hdr, int64_t *pre, TaskDev *td, const fdbb_task *tasks)
+{
+    const int64_t tile_pts = (int64_t)l.block * l.ppt;
+    int64_t units = 0;
+    for (int b = 0; b < ntasks; ++b) {
+        td[b].groups = l.parts ? task_groups(tasks[b]) : 1;
+        td[b].first_unit = pre[b] = units;
+        units += (tasks[b].n + tile_pts - 1) / tile_pts * td[b].groups;
+    }
+    pre[ntasks] = units;
+    hdr[0] = ntasks;
+    hdr[1] = units;
+    l.grid = (int)std::max<int64_t>(1, std::min<int64_t>(l.grid, units));
+}
 
 // What filling a task table found.
 struct TableInfo {
@@ -1085,8 +1212,7 @@ int fill_table(const fdbb_task *tasks, int ntasks, int cap, int block, int ppt, 
         if (rc) return fail(rc, "task " + std::to_string(b) + ": " + g_last_error);
         rc = check_alias(c);
         if (rc) return fail(rc, "task " + std::to_string(b) + ": " + g_last_error);
-        const bool jac = tasks[b].op == FDBB_OP_FLUX_JACOBIAN || (tasks[b].op == FDBB_OP_FUSED && tasks[b].out1);
-        if (jac) r.lds = std::max(r.lds, lds_bytes(tasks[b].op, tasks[b].dim, tasks[b].dtype, block, ppt));
+        if (writes_blocks(tasks[b])) r.lds = std::max(r.lds, lds_bytes(tasks[b].op, tasks[b].dim, tasks[b].dtype, block, ppt));
         for (int k = 0; k < c.nranges; ++k) {
             all[nall] = c.ranges[k];
             all[nall].task = b;
@@ -1099,7 +1225,8 @@ int fill_table(const fdbb_task *tasks, int ntasks, int cap, int block, int ppt, 
         td[b].op = tasks[b].op;
         td[b].dim = tasks[b].dim;
         td[b].dtype = tasks[b].dtype;
-        td[b].pad = 0;
+        td[b].groups = 1;
+        td[b].first_unit = pre[b];
     }
     // Across tasks: no output may overlap another task's input or output.
     std::sort(all, all + nall, [](const Range &x, const Range &y) { return x.lo < y.lo; });
@@ -1123,32 +1250,40 @@ int stage_tasks(fdbb_batch_plan *p, const fdbb_task *tasks, int ntasks)
 {
     if (ntasks < 0 || ntasks > p->capacity) return fail(FDBB_EINVAL, "ntasks exceeds the plan capacity");
     if (ntasks > 0 && !tasks) return fail(FDBB_EINVAL, "tasks must not be NULL");
+    DeviceInfo dev;
+    int rc = device_info(&dev);
+    if (rc) return rc;
     // Fill a private copy first, so that a rejected list neither waits for
     // nor disturbs an upload still reading the staging copy.
-    std::vector<unsigned char> tmp(p->bytes);
+    const size_t used = p->units_bytes() + table_task_offset(p->capacity) + (size_t)ntasks * sizeof(TaskDev);
+    std::vector<unsigned char> tmp(used);
     std::vector<Range> all((size_t)ntasks * 8);
     TableInfo info;
-    int rc = fill_table(tasks, ntasks, p->capacity, p->block, p->ppt, tmp.data(), all.data(), &info);
+    unsigned char *table = p->table(tmp.data());
+    rc = fill_table(tasks, ntasks, p->capacity, p->base.block, p->base.ppt, table, all.data(), &info);
     if (rc) return rc;
-    if (info.lds > p->lds) return fail(FDBB_EINVAL, "tasks need more LDS than the plan was created with");
+    if (info.lds > p->base.lds) return fail(FDBB_EINVAL, "tasks need more LDS than the plan was created with");
+    BatchLaunch l = pick_launch(tasks, ntasks, p->base, p->installed, dev);
+    if ((rc = set_lds_attr(l.kernel, l.lds, dev))) return rc;
+    fill_units(ntasks, l, p->unit_header(tmp.data()), p->unit_prefix(tmp.data()), table_tasks(table, p->capacity), tasks);
     // The previous upload must have consumed the staging copy.
     if (p->uploaded) {
         hipError_t e = hipEventSynchronize(p->uploaded);
         if (e != hipSuccess) return fail_hip(e, "hipEventSynchronize");
     }
-    const size_t used = table_task_offset(p->capacity) + (size_t)ntasks * sizeof(TaskDev);
     std::memcpy(p->host, tmp.data(), used);
     p->ntasks = ntasks;
     p->tiles = info.tiles;
     p->points = info.points;
-    p->cur_lds = info.lds;
+    p->list_lds = info.lds;
+    p->cur = l;
     return FDBB_OK;
 }
 
 int upload(fdbb_batch_plan *p, hipStream_t s)
 {
     // header, prefix sums and the tasks in use (not the whole capacity)
-    const size_t used = (size_t)((unsigned char *)(p->tasks(p->host) + p->ntasks) - p->host);
+    const size_t used = p->units_bytes() + table_task_offset(p->capacity) + (size_t)p->ntasks * sizeof(TaskDev);
     hipError_t e = hipMemcpyAsync(p->dev, p->host, used, hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return fail_hip(e, "hipMemcpyAsync");
     e = hipEventRecord(p->uploaded, s);
@@ -1156,27 +1291,75 @@ int upload(fdbb_batch_plan *p, hipStream_t s)
     return FDBB_OK;
 }
 
-// The persistent launch of p's table with `lds` bytes of dynamic LDS (the
-// reserve when captured into the graph, the current list's need when
-// launched directly: a list without Jacobian staging then runs at full
-// occupancy).
-int launch_plan(fdbb_batch_plan *p, hipStream_t s, size_t lds)
+// The general launch of p's table in the creation shape with `lds` bytes of
+// dynamic LDS; it takes any list that the plan accepts.
+int launch_general(fdbb_batch_plan *p, hipStream_t s, size_t lds)
 {
-    unsigned char *d = p->dev;
-    const TaskDev *tasks = p->tasks(d);
-    const int64_t *prefix = p->prefix(d);
-    const int64_t *header = p->header(d);
+    unsigned char *t = p->table(p->dev);
+    const TaskDev *tasks = table_tasks(t, p->capacity);
+    const int64_t *prefix = table_prefix(t);
+    const int64_t *header = table_header(t);
     void *args[] = {&tasks, &prefix, &header};
-    hipError_t e = hipLaunchKernel(p->kernel, dim3((unsigned)p->grid), dim3((unsigned)p->block), args, lds, s);
+    const BatchLaunch &l = p->base;
+    hipError_t e = hipLaunchKernel(l.kernel, dim3((unsigned)l.grid), dim3((unsigned)l.block), args, lds, s);
     if (e != hipSuccess) return fail_hip(e, "batch kernel launch");
     return FDBB_OK;
+}
+
+// The current list's own launch.
+int launch_list(fdbb_batch_plan *p, hipStream_t s)
+{
+    const TaskDev *tasks = table_tasks(p->table(p->dev), p->capacity);
+    const int64_t *prefix = p->unit_prefix(p->dev);
+    const int64_t *header = p->unit_header(p->dev);
+    void *args[] = {&tasks, &prefix, &header};
+    const BatchLaunch &l = p->cur;
+    hipError_t e = hipLaunchKernel(l.kernel, dim3((unsigned)l.grid), dim3((unsigned)l.block), args, l.lds, s);
+    if (e != hipSuccess) return fail_hip(e, "batch kernel launch");
+    return FDBB_OK;
+}
+
+// Captures what `launch` puts on a stream of its own and instantiates it.
+template <typename F>
+int capture(hipGraphExec_t *exec, F launch)
+{
+    hipStream_t cs = nullptr;
+    hipError_t e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking);
+    if (e != hipSuccess) return fail_hip(e, "hipStreamCreateWithFlags");
+    hipGraph_t graph = nullptr;
+    int rc = FDBB_OK;
+    e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
+    if (e == hipSuccess) {
+        rc = launch(cs);
+        hipError_t e2 = hipStreamEndCapture(cs, &graph);
+        if (rc == FDBB_OK && e2 != hipSuccess) rc = fail_hip(e2, "hipStreamEndCapture");
+    } else {
+        rc = fail_hip(e, "hipStreamBeginCapture");
+    }
+    (void)hipStreamDestroy(cs);
+    if (rc == FDBB_OK) {
+        e = hipGraphInstantiate(exec, graph, nullptr, nullptr, 0);
+        if (e != hipSuccess) rc = fail_hip(e, "hipGraphInstantiate");
+    }
+    if (graph) (void)hipGraphDestroy(graph);
+    return rc;
+}
+
+// Whether `s` is being captured (or cannot be asked because another stream
+// is: the launch then says so itself).
+bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
 }
 
 void free_plan(fdbb_batch_plan *p)
 {
     if (!p) return;
     if (p->exec) (void)hipGraphExecDestroy(p->exec);
-    if (p->graph) (void)hipGraphDestroy(p->graph);
+    if (p->general) (void)hipGraphExecDestroy(p->general);
     if (p->uploaded) (void)hipEventDestroy(p->uploaded);
     if (p->dev) (void)hipFree(p->dev);
     if (p->host) (void)hipHostFree(p->host);
@@ -1196,7 +1379,8 @@ int fdbb_batch_plan_create(const fdbb_task *tasks, int ntasks, int capacity, int
     if (capacity < 1 || capacity < ntasks) return fail(FDBB_EINVAL, "capacity must be >= max(1, ntasks)");
     if (ntasks > 0 && !tasks) return fail(FDBB_EINVAL, "tasks must not be NULL");
     int grid_per_cu = 0;
-    if (block == 0) {
+    const bool installed = block == 0;
+    if (installed) {
         // the installed configuration of the first task's storage type
         const BatchConfig bc = get_batch_config(ntasks > 0 ? tasks[0].dtype : FDBB_F64);
         block = bc.block, ppt = bc.ppt, nontemporal = bc.nt, grid_per_cu = bc.grid_per_cu, grid = 0;
@@ -1219,26 +1403,25 @@ int fdbb_batch_plan_create(const fdbb_task *tasks, int ntasks, int capacity, int
 
     fdbb_batch_plan *p = new fdbb_batch_plan();
     p->capacity = capacity;
-    p->block = block;
-    p->ppt = ppt;
-    p->kernel = kernel_batch(ppt, nontemporal);
-    p->nt = nontemporal;
+    p->installed = installed;
+    p->base.block = block;
+    p->base.ppt = ppt;
+    p->base.nt = nontemporal;
+    p->base.kernel = kernel_batch(ppt, nontemporal);
+    p->base.grid = grid > 0 ? grid : dev.cus * (grid_per_cu > 0 ? grid_per_cu : std::max(1, 2048 / block));
     (void)hipGetDevice(&p->device);
     // LDS for the largest Jacobian staging among the first task list; a plan
     // created empty reserves enough for any task (3D FP64 blocks).
     size_t lds = ntasks == 0 ? lds_bytes(FDBB_OP_FLUX_JACOBIAN, 3, FDBB_F64, block, ppt) : 0;
-    for (int b = 0; b < ntasks && tasks; ++b) {
-        const bool jac = tasks[b].op == FDBB_OP_FLUX_JACOBIAN || (tasks[b].op == FDBB_OP_FUSED && tasks[b].out1);
-        if (jac && tasks[b].dim >= 1 && tasks[b].dim <= 3 && (tasks[b].dtype == 0 || tasks[b].dtype == 1))
+    for (int b = 0; b < ntasks; ++b)
+        if (writes_blocks(tasks[b]))
             lds = std::max(lds, lds_bytes(tasks[b].op, tasks[b].dim, tasks[b].dtype, block, ppt));
-    }
-    p->lds = lds;
-    if ((rc = set_lds_attr(p->kernel, lds, dev))) {
+    p->base.lds = lds;
+    if ((rc = set_lds_attr(p->base.kernel, lds, dev))) {
         free_plan(p);
         return rc;
     }
-    p->grid = grid > 0 ? grid : dev.cus * (grid_per_cu > 0 ? grid_per_cu : std::max(1, 2048 / block));
-    p->bytes = table_bytes(capacity);
+    p->bytes = p->units_bytes() + table_bytes(capacity);
     hipError_t e = hipMalloc((void **)&p->dev, p->bytes);
     if (e != hipSuccess) {
         free_plan(p);
@@ -1265,26 +1448,12 @@ int fdbb_batch_plan_create(const fdbb_task *tasks, int ntasks, int capacity, int
         free_plan(p);
         return fail_hip(e, "hipMemcpy");
     }
-    // Capture the persistent launch once; later task lists only change the
-    // device table the kernel reads, so the graph is replayed unchanged.
-    hipStream_t cs = nullptr;
-    e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking);
-    if (e != hipSuccess) {
-        free_plan(p);
-        return fail_hip(e, "hipStreamCreate");
-    }
-    e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
-    if (e == hipSuccess) {
-        rc = launch_plan(p, cs, p->lds);
-        hipError_t e2 = hipStreamEndCapture(cs, &p->graph);
-        if (rc == FDBB_OK && e2 != hipSuccess) rc = fail_hip(e2, "hipStreamEndCapture");
-    } else {
-        rc = fail_hip(e, "hipStreamBeginCapture");
-    }
-    (void)hipStreamDestroy(cs);
-    if (rc == FDBB_OK) {
-        e = hipGraphInstantiate(&p->exec, p->graph, nullptr, nullptr, 0);
-        if (e != hipSuccess) rc = fail_hip(e, "hipGraphInstantiate");
+    // Capture the general launch, which later task lists replay unchanged (only
+    // the device table that the kernel reads changes), and the list's own.
+    rc = capture(&p->general, [&](hipStream_t cs) { return launch_general(p, cs, p->base.lds); });
+    if (rc == FDBB_OK && ntasks > 0 && p->cur.kernel != p->base.kernel) {
+        rc = capture(&p->exec, [&](hipStream_t cs) { return launch_list(p, cs); });
+        p->captured = p->cur;
     }
     if (rc) {
         const std::string msg = g_last_error;
@@ -1301,6 +1470,9 @@ int fdbb_batch_plan_update(fdbb_batch_plan *plan, const fdbb_task *tasks, int nt
     if (!plan) return fail(FDBB_EINVAL, "plan must not be NULL");
     int rc = stage_tasks(plan, tasks, ntasks);
     if (rc) return rc;
+    // A captured upload runs when its graph is replayed: until then the device
+    // table is another list's, so such a plan keeps to the general launch.
+    if (capturing((hipStream_t)stream)) plan->general_only = true;
     return upload(plan, (hipStream_t)stream);
 }
 
@@ -1309,12 +1481,16 @@ int fdbb_batch_exec(fdbb_batch_plan *plan, void *stream, int use_graph)
     g_last_error.clear();
     if (!plan) return fail(FDBB_EINVAL, "plan must not be NULL");
     if (plan->tiles == 0) return FDBB_OK;
-    if (use_graph) {
-        hipError_t e = hipGraphLaunch(plan->exec, (hipStream_t)stream);
-        if (e != hipSuccess) return fail_hip(e, "hipGraphLaunch");
-        return FDBB_OK;
+    // The list's own launch fits this list only.  A launch that is captured
+    // now may be replayed over a later list and is the general one.
+    if (plan->general_only || capturing((hipStream_t)stream)) {
+        if (!use_graph) return launch_general(plan, (hipStream_t)stream, plan->list_lds);
+        hipError_t e = hipGraphLaunch(plan->general, (hipStream_t)stream);
+        return e == hipSuccess ? FDBB_OK : fail_hip(e, "hipGraphLaunch");
     }
-    return launch_plan(plan, (hipStream_t)stream, plan->cur_lds);
+    if (!use_graph || !plan->exec || !(plan->cur == plan->captured)) return launch_list(plan, (hipStream_t)stream);
+    hipError_t e = hipGraphLaunch(plan->exec, (hipStream_t)stream);
+    return e == hipSuccess ? FDBB_OK : fail_hip(e, "hipGraphLaunch");
 }
 
 int fdbb_set_batch_config(int dtype, int block, int ppt, int grid_per_cu, int nontemporal)
@@ -1370,10 +1546,10 @@ int fdbb_get_batch_config(int dtype, int *block, int *ppt, int *grid_per_cu, int
 int fdbb_batch_plan_config(const fdbb_batch_plan *plan, int *block, int *ppt, int *grid, int *nontemporal)
 {
     if (!plan) return fail(FDBB_EINVAL, "plan must not be NULL");
-    if (block) *block = plan->block;
-    if (ppt) *ppt = plan->ppt;
-    if (grid) *grid = plan->grid;
-    if (nontemporal) *nontemporal = plan->nt;
+    if (block) *block = plan->base.block;
+    if (ppt) *ppt = plan->base.ppt;
+    if (grid) *grid = plan->base.grid;
+    if (nontemporal) *nontemporal = plan->base.nt;
     return FDBB_OK;
 }
 
@@ -1400,7 +1576,8 @@ int fdbb_batch_run_noalloc(const fdbb_task *tasks, int ntasks, int block, int pp
                                      " tasks, got " + std::to_string(ntasks));
     if (ntasks > 0 && !tasks) return fail(FDBB_EINVAL, "tasks must not be NULL");
     int grid_per_cu = 0;
-    if (block == 0) {
+    const bool installed = block == 0;
+    if (installed) {
         const BatchConfig bc = get_batch_config(ntasks > 0 ? tasks[0].dtype : FDBB_F64);
         block = bc.block, ppt = bc.ppt, nontemporal = bc.nt, grid_per_cu = bc.grid_per_cu, grid = 0;
     }
@@ -1424,9 +1601,18 @@ int fdbb_batch_run_noalloc(const fdbb_task *tasks, int ntasks, int block, int pp
     void *table = nullptr;
     const int se = batch_scratch(&table);
     if (se) return fail_hip((hipError_t)se, "hipGetSymbolAddress of the batch task table");
-    const void *kernel = kernel_batch(ppt, nontemporal);
-    if (!kernel) return fail(FDBB_EINVAL, "no batch kernel for this configuration");
-    if ((rc = set_lds_attr(kernel, info.lds, dev))) return rc;
+    BatchLaunch l;
+    l.block = block, l.ppt = ppt, l.nt = nontemporal;
+    l.kernel = kernel_batch(ppt, nontemporal);
+    l.lds = info.lds;
+    l.grid = grid > 0 ? grid : dev.cus * (grid_per_cu > 0 ? grid_per_cu : std::max(1, 2048 / block));
+    if (!l.kernel) return fail(FDBB_EINVAL, "no batch kernel for this configuration");
+    if ((rc = set_lds_attr(l.kernel, l.lds, dev))) return rc;
+    if (!capturing((hipStream_t)stream)) {
+        l = pick_launch(tasks, ntasks, l, installed, dev);
+        if ((rc = set_lds_attr(l.kernel, l.lds, dev))) return rc;
+    }
+    fill_units(ntasks, l, table_header(staging), table_prefix(staging), table_tasks(staging, kNoAllocMaxTasks), tasks);
     // From pageable host memory the copy completes before the call returns,
     // so the staging array is free again once it does; it is ordered on
     // `stream` before the launch that reads the table.
@@ -1438,8 +1624,7 @@ int fdbb_batch_run_noalloc(const fdbb_task *tasks, int ntasks, int block, int pp
     const int64_t *prefix = table_prefix(base);
     const int64_t *header = table_header(base);
     void *args[] = {&dtasks, &prefix, &header};
-    const int g = grid > 0 ? grid : dev.cus * (grid_per_cu > 0 ? grid_per_cu : std::max(1, 2048 / block));
-    e = hipLaunchKernel(kernel, dim3((unsigned)g), dim3((unsigned)block), args, info.lds, (hipStream_t)stream);
+    e = hipLaunchKernel(l.kernel, dim3((unsigned)l.grid), dim3((unsigned)l.block), args, l.lds, (hipStream_t)stream);
     if (e != hipSuccess) return fail_hip(e, "batch kernel launch");
     return FDBB_OK;
 }

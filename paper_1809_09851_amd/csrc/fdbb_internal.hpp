@@ -12,14 +12,30 @@
 namespace fdbb {
 
 // Device image of one batch task: the operation's arguments plus what the
-// persistent kernel needs to pick the tile function.
+// batch kernels need to pick the tile function and its parts.
 struct TaskDev {
     Args a;
     int32_t op;
     int32_t dim;
     int32_t dtype;
-    int32_t pad;
+    int32_t groups;      // sets of parts a tile is dealt in (1: the whole tile)
+    int64_t first_unit;  // the task's entry of the prefix sums
 };
+
+// Points of one span of a split launch (see Split).
+constexpr int64_t kSpanPoints = 131072;
+
+// The parts of set k of a fused pass or flux Jacobian dealt in `groups` sets:
+// the whole tile, one direction each, or all rows and then one direction's
+// blocks each.
+template <int D>
+__device__ __forceinline__ uint32_t batch_mask(int groups, uint32_t k)
+{
+    constexpr uint32_t dirs = all_directions<D>;
+    if (groups == 1) return dirs << kPartFields | dirs;
+    if (groups == D) return (1u << kPartFields | 1u) << k;
+    return k == 0 ? dirs << kPartFields : 1u << (k - 1);
+}
 
 // Largest workgroup of the kernels that stage Jacobian blocks (the fused
 // kernel and the batch kernel).  Bounding them at 256 threads lets the
@@ -56,11 +72,14 @@ const void *kernel_fused(int dim, int dtype, int ppt, bool nt, bool rows);  // r
 const void *kernel_adjoint(int dim, int dtype, int ppt, bool nt);
 const void *kernel_eigen(int family, int dim, int dtype, int ppt, bool nt);
 
-// Persistent batch kernel: void k(const TaskDev*, const int64_t* prefix,
-// const int64_t* header).  header = {ntasks, ntiles}; prefix has ntasks + 1
-// entries, prefix[b] = first tile of task b.  ppt 1, 2, 4 or 8; store_mode
-// 0 regular, 1 nt, 2 nt + sc1.
+// Batch kernels: void k(const TaskDev*, const int64_t* prefix, const int64_t*
+// header).  header = {ntasks, nunits}; prefix has ntasks + 1 entries,
+// prefix[b] = first unit of task b.  ppt 1, 2, 4 or 8 (the fused kernel: 1, 2
+// or 4, else null); store_mode 0 regular, 1 nt, 2 nt + sc1.  The general
+// kernel takes whole tiles (one unit each) of any batchable op; the fused one
+// lists of block-writing tasks of one dim and storage type.
 const void *kernel_batch(int ppt, int store_mode);
+const void *kernel_batch_fused(int dim, int dtype, int ppt, int store_mode);
 
 // The allocation-free batch entry point's fixed task table: room for
 // kNoAllocMaxTasks tasks in the layout of a plan's table (header, tile

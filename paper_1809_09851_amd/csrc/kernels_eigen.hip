@@ -18,8 +18,8 @@ __global__ __launch_bounds__(kMaxBlockStaged) void k_eigen(Args a, int64_t ntile
     const int64_t tile_pts = (int64_t)blockDim.x * P;
     const uint32_t units = (uint32_t)ntiles * sp.groups;
     for (uint32_t u = blockIdx.x; u < units; u += gridDim.x) {
-        const Unit w = unit_of(sp, (uint32_t)ntiles, u);
-        tile_eigen<D, T, P, NT>(a, w.tile * tile_pts, w.mask, lds);
+        const Unit w = unit_of(sp.groups, sp.span, (uint32_t)ntiles, u);
+        tile_eigen<D, T, P, NT>(a, w.tile * tile_pts, sp.mask[w.set], lds);
     }
 }
 
