@@ -17,6 +17,7 @@ enum : int32_t {
     kFlagInPlace = 1,  // K -> K transform with output == input: skip the rho store
     kFlagRight = 4,    // characteristic product with R (else with L)
     kFlagOneDir = 8,   // flux of direction Args::dir only, as K fields
+    kFlagShared = 16,  // two inputs are near views of the same points
 };
 
 // One operation on one field-set group (the device image of fdbb_task).
@@ -293,9 +294,33 @@ __device__ __forceinline__ void tile_prim2cons(const Args &a, int64_t tile0)
     }
 }
 
-// Roe-averaged state between the states in in0 (left) and in1 (right).
-// Per chunk, the left states are folded into weighted sums before the right
-// states are loaded, so that one side's raw state is live at a time.
+// Folds the raw states u of a chunk into the weighted sums; returns the
+// weights in w.
+template <int D, int W>
+__device__ __forceinline__ void roe_fold(const Gas &gas, const double (&u)[D + 2][W], double (&sum)[W][D + 1],
+                                         double (&w)[W])
+{
+    constexpr int K = D + 2;
+#pragma unroll
+    for (int j = 0; j < W; ++j) {
+        double uj[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) uj[k] = u[k][j];
+        w[j] = roe_accumulate<D>(gas, uj, sum[j]);
+        if constexpr (W > 1) __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// Roe-averaged state between the states in in0 (left) and in1 (right); bound
+// by HBM.  Two sides that are one state shifted by a few cells (kFlagShared:
+// the faces of a grid) read every line twice: regular loads leave it in cache
+// for the other side, and at one point per thread both sides are asked for at
+// once.  3D FP64, one cell apart, 8 M points: 196 us with the non-temporal
+// loads below, 111 (5.8 TB/s of what has to move); 1000 cells apart 163 and
+// 117; 2 M points 45 and 34.  Sides of their own are streams that no one reads
+// again: non-temporal loads, the left states folded into weighted sums before
+// the right ones are asked for, so that few streams are open (8 M: 160 us;
+// both at once 168).
 template <int D, typename T, int P, int NT>
 __device__ __forceinline__ void tile_roe(const Args &a, int64_t tile0)
 {
@@ -311,31 +336,23 @@ __device__ __forceinline__ void tile_roe(const Args &a, int64_t tile0)
         for (int j = 0; j < W; ++j)
 #pragma unroll
             for (int k = 0; k <= D; ++k) sum[j][k] = 0.0;
-        {
-            double u[K][W];
-            L.template load_fields<K, true>(a.in0, a.ld_in0, c, u);
-#pragma unroll
-            for (int j = 0; j < W; ++j) {
-                double uj[K];
-#pragma unroll
-                for (int k = 0; k < K; ++k) uj[k] = u[k][j];
-                wl[j] = roe_accumulate<D>(a.gas, uj, sum[j]);
-                __builtin_amdgcn_sched_barrier(0);
-            }
+        double ul[K][W], ur[K][W];
+        if (a.flags & kFlagShared) {
+            // the barriers keep the branches apart: merged, the loads of one
+            // would take the other's cache policy and order
+            __builtin_amdgcn_sched_barrier(0);
+            L.template load_fields<K>(a.in0, a.ld_in0, c, ul);
+            if constexpr (W > 1) roe_fold<D, W>(a.gas, ul, sum, wl);
+            L.template load_fields<K>(a.in1, a.ld_in1, c, ur);
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (W == 1) roe_fold<D, W>(a.gas, ul, sum, wl);
+        } else {
+            L.template load_fields<K, true>(a.in0, a.ld_in0, c, ul);
+            roe_fold<D, W>(a.gas, ul, sum, wl);
+            __builtin_amdgcn_sched_barrier(0);
+            L.template load_fields<K, true>(a.in1, a.ld_in1, c, ur);
         }
-        __builtin_amdgcn_sched_barrier(0);
-        {
-            double u[K][W];
-            L.template load_fields<K, true>(a.in1, a.ld_in1, c, u);
-#pragma unroll
-            for (int j = 0; j < W; ++j) {
-                double uj[K];
-#pragma unroll
-                for (int k = 0; k < K; ++k) uj[k] = u[k][j];
-                wr[j] = roe_accumulate<D>(a.gas, uj, sum[j]);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
+        roe_fold<D, W>(a.gas, ur, sum, wr);
         double out[K][W];
 #pragma unroll
         for (int j = 0; j < W; ++j) {

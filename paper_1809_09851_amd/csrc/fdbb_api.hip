@@ -553,6 +553,21 @@ int begin(Call &c, int op, int dim, double gamma, int dtype, int64_t n)
 // Fills c for any op from the task-style argument list; shared by the
 // single-call entry points and the batch plans.  `mode` selects R (1) or L
 // (0) for the characteristic products.
+// Whether in0 and in1 are views of the same K rows, shifted by so few points
+// that what one side read is still cached when the other asks for it: the
+// lines of that distance, a quarter of the last-level cache at most.  Roe
+// average of 8 M points, 3D FP64, time over that of unrelated sides' path:
+// 0.57 at 1 cell, 0.72 at 1000, 0.85 at 1.5 M (60 MB), 1.04 at 7 M (280 MB).
+constexpr int64_t kNearBytes = (int64_t)64 << 20;
+
+bool near_views(const fdbb_task &t, int K)
+{
+    if (t.ld_in0 != t.ld_in1) return false;
+    const uintptr_t l = (uintptr_t)t.in0, r = (uintptr_t)t.in1;
+    const int64_t shift = (int64_t)(l < r ? r - l : l - r);  // bytes
+    return shift < t.n * (int64_t)elem_size(t.dtype) && shift * K <= kNearBytes;
+}
+
 int build_call(Call &c, const fdbb_task &t, int mode = 0)
 {
     int rc = begin(c, t.op, t.dim, t.gamma, t.dtype, t.n);
@@ -630,6 +645,7 @@ int build_call(Call &c, const fdbb_task &t, int mode = 0)
         c.inplace_ok = true;
         a.in0 = t.in0, a.ld_in0 = t.ld_in0, a.in1 = t.in1, a.ld_in1 = t.ld_in1;
         a.out0 = t.out0, a.ld_out0 = t.ld_out0;
+        if (near_views(t, K)) a.flags |= kFlagShared;
         if ((rc = add_fields(c, t.in0, t.ld_in0, K, 1, true, true, "UL"))) return rc;
         if ((rc = add_fields(c, t.in1, t.ld_in1, K, 1, true, true, "UR"))) return rc;
         if ((rc = add_fields(c, t.out0, t.ld_out0, K, 1, false, true, "Uh"))) return rc;
