@@ -249,7 +249,10 @@ int fdbb_viscous_flux(int dim, double mu, double kappa, int dtype, const void *U
  * written with streaming stores, 0: regular stores; a streaming store sets
  * the nt cache-policy bit, and in the fused pass, flux Jacobian,
  * eigenvector blocks, flux and Riemann invariants, in FP64 cons2prim and
- * prim2cons and in FP32 |v|^2 also sc1, the device-scope bit).  Returns
+ * prim2cons and in FP32 |v|^2 also sc1, the device-scope bit).  Large calls of an op that
+ * writes a field set at one point per thread without a grid cap take at least
+ * 512 threads where the output rows do not start on cache lines, and in the
+ * 2D and 3D flux and Riemann invariants regular stores.  Returns
  * FDBB_EINVAL for values outside these sets.  The table is process-wide and
  * safe to update while other threads launch. */
 int fdbb_set_launch_config(int op, int dim, int dtype, int block, int ppt, int grid_cap,

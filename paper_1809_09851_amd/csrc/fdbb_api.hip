@@ -503,13 +503,52 @@ int set_lds_attr(const void *fn, size_t lds, const DeviceInfo &dev)
     return FDBB_OK;  // table full (more kernels than exist): the limit is raised anyway
 }
 
+// Output rows that start inside a cache line (packed tensors of odd length,
+// offset views) split a line between every two workgroups, which usually run
+// on different XCDs and each write their part of it to memory.  Longer runs
+// leave fewer such lines: the pointwise ops that write a field set take at
+// least 512 threads (time over the table's shape, mean over dims, types and
+// packed sets of 1 to 12 M points: characteristic product 0.89, Roe average
+// and adjoint 0.90, viscous flux and characteristic transforms 0.94).  The
+// streaming stores of the flux and the Riemann invariants carry sc1, which
+// writes parts of lines through at once; in 2D and 3D regular stores, which
+// L2 merges, are faster then (flux 0.77, 0.91, 0.64, 0.81 for 2D FP32, FP64,
+// 3D FP32, FP64; invariants 0.87, 0.96, 0.81, 0.92; 1D 0.98 to 1.13, left
+// alone).  Below 2^19 points the rows stay in cache and nothing changes.
+constexpr int64_t kLineBytes = 128;
+constexpr int64_t kRaggedMin = (int64_t)1 << 19;
+constexpr int kRaggedBlock = 512;
+
+Config fit_rows(const Call &c, Config cfg)
+{
+    if (c.a.n < kRaggedMin || cfg.ppt != 1 || cfg.grid_cap != 0 || cfg.block >= kRaggedBlock) return cfg;
+    const uintptr_t starts = (uintptr_t)c.a.out0 | (uintptr_t)(c.a.ld_out0 * (int64_t)elem_size(c.dtype));
+    if (starts % kLineBytes == 0) return cfg;
+    switch (family_of(c.op)) {
+    case kFamFlux:
+    case kFamRiemann:
+        if (c.dim == 1) return cfg;
+        cfg.nt = 0;
+        break;
+    case kFamAdjoint:
+    case kFamCharApply:
+    case kFamRoe:
+    case kFamViscous:
+    case kFamCons2Char:
+    case kFamChar2Cons: break;
+    default: return cfg;
+    }
+    cfg.block = kRaggedBlock;
+    return cfg;
+}
+
 int launch(Call &c, void *stream)
 {
     if (c.a.n == 0) return FDBB_OK;
     int rc = check_alias(c);
     if (rc) return rc;
 
-    const Config cfg = get_config(c.op, c.dim, c.dtype, c.a.n);
+    const Config cfg = fit_rows(c, get_config(c.op, c.dim, c.dtype, c.a.n));
     const void *fn = kernel_for(c.op, c.dim, c.dtype, cfg.ppt, cfg.nt != 0);
     if (!fn) return fail(FDBB_EINVAL, "no kernel for this configuration");
     DeviceInfo dev;
