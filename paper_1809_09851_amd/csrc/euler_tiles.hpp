@@ -106,11 +106,13 @@ __device__ __forceinline__ void load_chunk(const T *__restrict__ p, int cnt, dou
 // The launch configuration chooses between regular and streaming stores;
 // each kernel family's picker fixes which streaming flavour it uses, from
 // timings of both taken alternately in one process on the same buffers.
-// The single-launch kernels that write K x K blocks (fused pass, flux
-// Jacobian, eigenvector blocks) stream with nt + sc1, under which they ran
-// 1.8-3.5 % faster on this device than with nt alone (a plain write
-// stream: 7.0 against 6.7-6.8 TB/s).  The persistent batch kernel takes any
-// of the three modes; its autotuned configuration picks one.
+// With many waves resident the kernels that write K x K blocks (fused pass,
+// flux Jacobian, eigenvector blocks) ran 1.8-3.5 % faster with nt + sc1 (a
+// plain write stream: 7.0 against 6.7-6.8 TB/s); with the few that 3D FP64
+// keeps resident nt alone is ahead, but for batches.  sc1 writes a part of
+// a cache line through at once, so rows that start inside lines want one of
+// the other two.  The batch kernels take any of the three modes; their
+// autotuned configuration picks one.
 enum : int { kStoreRegular = 0, kStoreNT = 1, kStoreNTSc1 = 2 };
 
 // No compiler builtin sets sc1 on a global store, hence the inline

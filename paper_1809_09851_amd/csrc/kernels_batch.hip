@@ -6,7 +6,9 @@
 // deal balances without a shared counter.  The grid is part of the launch
 // configuration: a few workgroups per compute unit make the launch
 // persistent, a grid near the tile count leaves the order of tiles to the
-// hardware dispatcher (the tuned FP32 shape).
+// hardware dispatcher, which the lists that reach this kernel under the
+// installed configurations prefer (lists of block-writing tasks of one dim
+// and storage type have a kernel of their own).
 #include "fdbb_internal.hpp"
 
 #include <atomic>
