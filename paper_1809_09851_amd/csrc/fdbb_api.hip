@@ -363,9 +363,13 @@ struct SplitPlan {
 // that of one workgroup per tile, every part of it, at its best shape):
 //   kByDirection (FP64): 0.87 at 1 000 003 points, 0.95 from 4 M to 2^24;
 //     rows apart 0.88 / 0.96, so the state is read three times, not four;
-//   kFieldsApart (FP32): 0.95 at 1 000 003 points, 0.84 at 4 M, 0.85 at 12 M,
-//     by direction 0.96 / 0.88 / 0.88; beyond 4 GiB of blocks every split
-//     loses (1.02-1.3 at 2^24 and 25 M), and the whole tile is taken;
+//   kFieldsApart (FP32): 0.85-0.95 from 1 000 003 to 1.5 M points (by
+//     direction 2-4 % slower), but only while a program's arrays together stay
+//     below about 4 GB: at 2.5 M points 0.87 over one set of arrays, 0.85 over
+//     4 and 1.21 over 12 in turn (whole tile 0.96, 0.97, 0.93), at 8 M 0.86
+//     over one and 1.24 over 4 (0.99, 0.99); up to 512 MiB of blocks even 12
+//     sets gain (0.93), beyond the whole tile is taken.  Eigenvector blocks
+//     keep their split (0.85-0.89 over three sets at every size);
 //   1D and 2D (K*K a power of two or 9): the whole tile, a split gained
 //     nothing (2D FP64 0.92 against 0.93, 2D FP32 1.02 against 1.00);
 //   blocks that fit in the 256 MB last-level cache: the whole tile (200 003
@@ -373,7 +377,7 @@ struct SplitPlan {
 // Spans of 131072 points: 32768 is level in FP64 (0.933 against 0.930 over 16
 // buffers), 10-20 % slower in FP32; one span over the whole call reads the
 // state from HBM again (2^24 FP64: 1.05).
-constexpr int64_t kApartMaxBytes = (int64_t)4 << 30;
+constexpr int64_t kApartMaxBytes = (int64_t)512 << 20;
 constexpr int64_t kLastLevelBytes = (int64_t)256 << 20;
 enum { kWhole = 0, kByDirection = 1, kFieldsApart = 2 };
 
@@ -442,7 +446,7 @@ SplitPlan split_of(const Call &c, int64_t tile_pts)
 // 8 waves 0.89, 24 waves 0.99).  A whole tile at one point per thread takes
 // 3072 B in 2D FP64 (fused pass 8 waves 0.93, 16 waves 1.00), 2048 B in 1D
 // FP64 (16 waves 0.95, 24 waves 0.97, 12 waves 1.01) and 6208 B in FP32 (3D
-// beyond 4 GiB: 16 waves 0.95); more points per thread keep what their LDS
+// beyond 512 MiB: 16 waves 0.93-1.00); more points per thread keep what their LDS
 // leaves, and so do blocks that stay in the last-level cache.
 constexpr int kMaxWaves = 32, kMinWaves = 8;
 constexpr int kWrittenPerLane = 900;
@@ -1151,9 +1155,10 @@ int task_groups(const fdbb_task &t)
 //     waves 1.09, 6 waves 1.1, unlimited 0.97); from 32 GiB of blocks the
 //     whole tile at 4 waves wins (72.8 M in 512 tasks 0.97, by parts 1.01;
 //     55 M 0.96 and 0.96; 40 M 0.96 and 0.88);
-//   3D FP32, parts, no bound: 0.92 / 0.73; 8 waves 1.2, and beyond 4 GiB the
-//     whole tile at 16 waves as in a single call (25 M 0.95, 18 M 0.99, by
-//     parts 1.12 and 1.04);
+//   3D FP32, parts without a bound up to 512 MiB of blocks, as in a single
+//     call: 0.64 at 1.5 M points; beyond the whole tile at 16 waves: 0.79 at 3
+//     M, 0.94 at 10 M, 0.93 at 8.7 M over three sets of arrays in turn (parts
+//     0.72, 1.00, 1.02), 25 M 0.95;
 //   2D whole tile: FP64 8 waves 0.95 (unlimited 1.03), FP32 0.72; 1D 0.78
 //     and 0.53 without a bound (16 waves 0.78 and 0.76);
 //   lists that fit in the last-level cache: the whole tile, no bound and, in
