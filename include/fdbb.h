@@ -354,8 +354,9 @@ int fdbb_batch_plan_update(fdbb_batch_plan *plan, const fdbb_task *tasks, int nt
  * (kernel, shape and LDS), and is a direct launch otherwise; 0 always launches
  * directly.  While `stream` is being captured, and for good once a list was
  * uploaded on a capturing stream, the launch is the general one in the shape
- * the plan was created with, which stays right when the capturing graph is
- * replayed over later lists. */
+ * the plan was created with and with the LDS that the plan holds, recorded
+ * for an empty list too: it stays right when the capturing graph is replayed
+ * over later lists. */
 int fdbb_batch_exec(fdbb_batch_plan *plan, void *stream, int use_graph);
 
 /* The batch configuration that plans created with block == 0, the

@@ -1115,7 +1115,6 @@ struct fdbb_batch_plan {
     BatchLaunch base;           // as created; base.lds is the staging a task list may need
     BatchLaunch cur;            // the current task list's own launch
     BatchLaunch captured;       // what `exec` launches with
-    size_t list_lds = 0;        // staging of the current task list in the creation shape
     int64_t points = 0;
     int64_t tiles = 0;          // of the creation shape
     unsigned char *dev = nullptr;   // task table, capacity `capacity`
@@ -1335,7 +1334,6 @@ int stage_tasks(fdbb_batch_plan *p, const fdbb_task *tasks, int ntasks)
     p->ntasks = ntasks;
     p->tiles = info.tiles;
     p->points = info.points;
-    p->list_lds = info.lds;
     p->cur = l;
     return FDBB_OK;
 }
@@ -1351,9 +1349,11 @@ int upload(fdbb_batch_plan *p, hipStream_t s)
     return FDBB_OK;
 }
 
-// The general launch of p's table in the creation shape with `lds` bytes of
-// dynamic LDS; it takes any list that the plan accepts.
-int launch_general(fdbb_batch_plan *p, hipStream_t s, size_t lds)
+// The general launch of p's table in the creation shape.  It takes any list
+// that the plan accepts, so its dynamic LDS is what any of them may stage: a
+// launch that is captured, or that runs before a captured upload does, may
+// find another list in the table than the current one.
+int launch_general(fdbb_batch_plan *p, hipStream_t s)
 {
     unsigned char *t = p->table(p->dev);
     const TaskDev *tasks = table_tasks(t, p->capacity);
@@ -1361,7 +1361,7 @@ int launch_general(fdbb_batch_plan *p, hipStream_t s, size_t lds)
     const int64_t *header = table_header(t);
     void *args[] = {&tasks, &prefix, &header};
     const BatchLaunch &l = p->base;
-    hipError_t e = hipLaunchKernel(l.kernel, dim3((unsigned)l.grid), dim3((unsigned)l.block), args, lds, s);
+    hipError_t e = hipLaunchKernel(l.kernel, dim3((unsigned)l.grid), dim3((unsigned)l.block), args, l.lds, s);
     if (e != hipSuccess) return fail_hip(e, "batch kernel launch");
     return FDBB_OK;
 }
@@ -1510,7 +1510,7 @@ int fdbb_batch_plan_create(const fdbb_task *tasks, int ntasks, int capacity, int
     }
     // Capture the general launch, which later task lists replay unchanged (only
     // the device table that the kernel reads changes), and the list's own.
-    rc = capture(&p->general, [&](hipStream_t cs) { return launch_general(p, cs, p->base.lds); });
+    rc = capture(&p->general, [&](hipStream_t cs) { return launch_general(p, cs); });
     if (rc == FDBB_OK && ntasks > 0 && p->cur.kernel != p->base.kernel) {
         rc = capture(&p->exec, [&](hipStream_t cs) { return launch_list(p, cs); });
         p->captured = p->cur;
@@ -1540,14 +1540,15 @@ int fdbb_batch_exec(fdbb_batch_plan *plan, void *stream, int use_graph)
 {
     g_last_error.clear();
     if (!plan) return fail(FDBB_EINVAL, "plan must not be NULL");
-    if (plan->tiles == 0) return FDBB_OK;
     // The list's own launch fits this list only.  A launch that is captured
-    // now may be replayed over a later list and is the general one.
+    // now, over an empty list too, may be replayed over a later list and is
+    // the general one.
     if (plan->general_only || capturing((hipStream_t)stream)) {
-        if (!use_graph) return launch_general(plan, (hipStream_t)stream, plan->list_lds);
+        if (!use_graph) return launch_general(plan, (hipStream_t)stream);
         hipError_t e = hipGraphLaunch(plan->general, (hipStream_t)stream);
         return e == hipSuccess ? FDBB_OK : fail_hip(e, "hipGraphLaunch");
     }
+    if (plan->tiles == 0) return FDBB_OK;
     if (!use_graph || !plan->exec || !(plan->cur == plan->captured)) return launch_list(plan, (hipStream_t)stream);
     hipError_t e = hipGraphLaunch(plan->exec, (hipStream_t)stream);
     return e == hipSuccess ? FDBB_OK : fail_hip(e, "hipGraphLaunch");

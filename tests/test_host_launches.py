@@ -1,0 +1,44 @@
+"""What the library's host code launches, copies and refuses, checked without
+a device (see hip_host.py)."""
+import pytest
+
+import hip_host
+
+STAGED_3D_F64 = 256 * 25 * 8  # LDS of 3D FP64 blocks at 256 threads, one point each
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    stand_ins = hip_host.build(tmp_path_factory.mktemp("hip"))
+    return lambda script: hip_host.run(stand_ins, script)
+
+
+@pytest.mark.parametrize("first", ("[]", "[task(FUSED, 3, 1000)]"))
+@pytest.mark.parametrize("at_capture", ("[task(FLUX, 3, 100)]", "[]"))
+def test_captured_launch_has_room_for_every_later_list(run, first, at_capture):
+    """A launch recorded over a list without block-writing tasks, or over an
+    empty one, is replayed over lists that stage 3D FP64 blocks in LDS."""
+    run(f"""
+s = h.stream()
+plan = h.plan({first}, block=256)
+assert h.update(plan, {at_capture}, s) == 0
+graph = h.capture(s, lambda: h.run(plan, s, 0))
+assert h.update(plan, [task(FUSED, 3, 1000), task(CONS2PRIM, 2, 50)], s) == 0
+h.replay(graph, s)
+(l,) = h.launches()
+assert l.replay and l.units == 5 and l.lds >= {STAGED_3D_F64}, l
+""")
+
+
+def test_launch_between_a_captured_upload_and_its_replay(run):
+    """The table on the device is still the list before: the launch has the
+    LDS which that one stages."""
+    run(f"""
+s = h.stream()
+plan = h.plan([task(FUSED, 3, 1000), task(CONS2PRIM, 2, 50)], block=256)
+for later in ([task(FLUX, 3, 100)], []):
+    graph = h.capture(s, lambda: h.update(plan, later, s))
+    h.run(plan, s, 0)
+    (l,) = h.launches()
+    assert l.units == 5 and l.lds >= {STAGED_3D_F64}, l
+""")
