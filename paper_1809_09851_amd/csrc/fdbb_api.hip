@@ -1121,8 +1121,7 @@ struct fdbb_batch_plan {
     unsigned char *host = nullptr;  // pinned staging copy of the same layout
     size_t bytes = 0;
     hipEvent_t uploaded = nullptr;  // the last upload has left the staging copy
-    hipGraphExec_t general = nullptr;  // the general launch in the creation shape
-    hipGraphExec_t exec = nullptr;     // the first list's own launch, if another
+    hipGraphExec_t exec = nullptr;  // the first list's own launch, if another kernel's than the general one
 
     size_t units_bytes() const { return ((2 + (size_t)capacity + 1) * sizeof(int64_t) + 63) & ~(size_t)63; }
     int64_t *unit_header(unsigned char *t) const { return reinterpret_cast<int64_t *>(t); }
@@ -1419,7 +1418,6 @@ void free_plan(fdbb_batch_plan *p)
 {
     if (!p) return;
     if (p->exec) (void)hipGraphExecDestroy(p->exec);
-    if (p->general) (void)hipGraphExecDestroy(p->general);
     if (p->uploaded) (void)hipEventDestroy(p->uploaded);
     if (p->dev) (void)hipFree(p->dev);
     if (p->host) (void)hipHostFree(p->host);
@@ -1508,10 +1506,9 @@ int fdbb_batch_plan_create(const fdbb_task *tasks, int ntasks, int capacity, int
         free_plan(p);
         return fail_hip(e, "hipMemcpy");
     }
-    // Capture the general launch, which later task lists replay unchanged (only
-    // the device table that the kernel reads changes), and the list's own.
-    rc = capture(&p->general, [&](hipStream_t cs) { return launch_general(p, cs); });
-    if (rc == FDBB_OK && ntasks > 0 && p->cur.kernel != p->base.kernel) {
+    // Capture the list's own launch: it is replayed for every list that wants
+    // the same one (only the device table that the kernel reads changes).
+    if (ntasks > 0 && p->cur.kernel != p->base.kernel) {
         rc = capture(&p->exec, [&](hipStream_t cs) { return launch_list(p, cs); });
         p->captured = p->cur;
     }
@@ -1542,12 +1539,9 @@ int fdbb_batch_exec(fdbb_batch_plan *plan, void *stream, int use_graph)
     if (!plan) return fail(FDBB_EINVAL, "plan must not be NULL");
     // The list's own launch fits this list only.  A launch that is captured
     // now, over an empty list too, may be replayed over a later list and is
-    // the general one.
-    if (plan->general_only || capturing((hipStream_t)stream)) {
-        if (!use_graph) return launch_general(plan, (hipStream_t)stream);
-        hipError_t e = hipGraphLaunch(plan->general, (hipStream_t)stream);
-        return e == hipSuccess ? FDBB_OK : fail_hip(e, "hipGraphLaunch");
-    }
+    // the general one, launched directly: a graph launch on a stream that is
+    // being captured runs at once and leaves nothing in the capture.
+    if (plan->general_only || capturing((hipStream_t)stream)) return launch_general(plan, (hipStream_t)stream);
     if (plan->tiles == 0) return FDBB_OK;
     if (!use_graph || !plan->exec || !(plan->cur == plan->captured)) return launch_list(plan, (hipStream_t)stream);
     hipError_t e = hipGraphLaunch(plan->exec, (hipStream_t)stream);

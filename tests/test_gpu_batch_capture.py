@@ -24,17 +24,18 @@ def flux_only(seed=70):
 
 @pytest.mark.parametrize("created", ("empty", "with blocks"))
 @pytest.mark.parametrize("at_capture", ("flux", "empty"))
-def test_captured_over_a_list_that_stages_nothing(created, at_capture):
+@pytest.mark.parametrize("graph", (False, True))
+def test_captured_over_a_list_that_stages_nothing(created, at_capture, graph):
     lists = uniform(3, "f64", SIZES), mixed(3, "f64", SIZES), flux_only()
     plan = B.Plan(tasks(lists[0]) if created == "with blocks" else [], capacity=len(SIZES))
     plan.update(tasks(flux_only()) if at_capture == "flux" else [])
     recorded = torch.cuda.CUDAGraph()
     with torch.cuda.graph(recorded):
-        plan.run(graph=False)
+        plan.run(graph=graph)
     for blocks in (*lists, *lists):
         plan.update(tasks(blocks))
         checked(blocks, recorded.replay)
-        checked(blocks, lambda: plan.run(graph=False))
+        checked(blocks, lambda: plan.run(graph=graph))
     del recorded
     plan.close()
 

@@ -42,3 +42,18 @@ for later in ([task(FLUX, 3, 100)], []):
     (l,) = h.launches()
     assert l.units == 5 and l.lds >= {STAGED_3D_F64}, l
 """)
+
+
+@pytest.mark.parametrize("listed", ("[task(FUSED, 3, 1000)]", "[task(FLUX, 3, 100)]", "[]"))
+def test_graph_launch_is_recorded_by_a_capture(run, listed):
+    """The runtime runs a graph launch on a capturing stream at once and
+    records nothing: run(graph=True) under capture has to be a launch."""
+    run(f"""
+s = h.stream()
+plan = h.plan({listed})
+graph = h.capture(s, lambda: h.run(plan, s, 1))
+assert not h.launches()
+for _ in range(2):
+    h.replay(graph, s)
+    assert len(h.launches()) == 1
+""")
