@@ -325,7 +325,7 @@ typedef struct fdbb_batch_plan fdbb_batch_plan;
 /* Create a plan for up to `capacity` tasks (>= ntasks) and load `tasks`
  * into it.  Each task is validated as its single-call entry point would be.
  * The plan owns a device copy of the task table, the tile prefix sums and
- * HIP graphs of one kernel with at most `grid` workgroups of `block`
+ * the HIP graph of one kernel with at most `grid` workgroups of `block`
  * threads (64..256 in multiples of 64; grid 0 picks one sized to the
  * device), `ppt` points per thread (1, 2, 4 or 8) and regular (0),
  * streaming (1: the nt bit) or streaming device-coherent (2: nt and sc1)
@@ -349,10 +349,10 @@ int fdbb_batch_plan_create(const fdbb_task *tasks, int ntasks, int capacity, int
 int fdbb_batch_plan_update(fdbb_batch_plan *plan, const fdbb_task *tasks, int ntasks,
                            void *stream);
 
-/* Run the plan's launch on `stream`.  use_graph != 0 replays the HIP graph
- * captured at creation where the current task list wants the launch it holds
- * (kernel, shape and LDS), and is a direct launch otherwise; 0 always launches
- * directly.  While `stream` is being captured, and for good once a list was
+/* Run the plan's launch on `stream`.  use_graph != 0 replays the HIP graph of
+ * the first task list's launch, captured at creation, where the current list
+ * wants the same one (kernel, shape, grid and LDS); otherwise, and for a plan
+ * created empty, it is a direct launch.  0 always launches directly.  While `stream` is being captured, and for good once a list was
  * uploaded on a capturing stream, the launch is the general one in the shape
  * the plan was created with and with the LDS that the plan holds, recorded
  * for an empty list too: it stays right when the capturing graph is replayed

@@ -1121,7 +1121,7 @@ struct fdbb_batch_plan {
     unsigned char *host = nullptr;  // pinned staging copy of the same layout
     size_t bytes = 0;
     hipEvent_t uploaded = nullptr;  // the last upload has left the staging copy
-    hipGraphExec_t exec = nullptr;  // the first list's own launch, if another kernel's than the general one
+    hipGraphExec_t exec = nullptr;  // the first list's own launch (none for a plan created empty)
 
     size_t units_bytes() const { return ((2 + (size_t)capacity + 1) * sizeof(int64_t) + 63) & ~(size_t)63; }
     int64_t *unit_header(unsigned char *t) const { return reinterpret_cast<int64_t *>(t); }
@@ -1508,7 +1508,7 @@ int fdbb_batch_plan_create(const fdbb_task *tasks, int ntasks, int capacity, int
     }
     // Capture the list's own launch: it is replayed for every list that wants
     // the same one (only the device table that the kernel reads changes).
-    if (ntasks > 0 && p->cur.kernel != p->base.kernel) {
+    if (ntasks > 0) {
         rc = capture(&p->exec, [&](hipStream_t cs) { return launch_list(p, cs); });
         p->captured = p->cur;
     }

@@ -57,3 +57,32 @@ for _ in range(2):
     h.replay(graph, s)
     assert len(h.launches()) == 1
 """)
+
+
+LISTS = ("[task(FUSED, 3, 1000)]", "[task(FUSED, 3, 1000), task(FLUX, 2, 70)]", "[task(FLUX, 1, 500)]",
+         "[task(JACOBIAN, 2, 300, F32), task(FUSED, 2, 9, F32)]")
+
+
+@pytest.mark.parametrize("block,ppt", ((0, 1), (256, 1), (64, 2), (64, 8)))
+@pytest.mark.parametrize("listed", LISTS)
+def test_graph_holds_the_first_lists_launch(run, listed, block, ppt):
+    """run(graph=True) replays a graph for every kind of list that a plan is
+    created with, and for a later list that wants the same launch."""
+    run(f"""
+s = h.stream()
+tasks = {listed}
+plan = h.plan(tasks, block={block}, ppt={ppt})
+h.run(plan, s, 1)
+h.run(plan, s, 0)
+replayed, direct = h.launches()
+assert replayed.replay and not direct.replay
+assert str(replayed).split()[:-1] == str(direct).split()[:-1]
+assert h.update(plan, {listed}, s) == 0
+h.run(plan, s, 1)
+(l,) = h.launches()
+assert l.replay
+assert h.update(plan, tasks + [task(FLUX, 1, 40000)], s) == 0
+h.run(plan, s, 1)
+(l,) = h.launches()
+assert not l.replay and l.units > replayed.units
+""")
