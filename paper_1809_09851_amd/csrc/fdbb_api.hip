@@ -1404,14 +1404,14 @@ int capture(hipGraphExec_t *exec, F launch)
     return rc;
 }
 
-// Whether `s` is being captured (or cannot be asked because another stream
-// is: the launch then says so itself).
+// Whether `s` is being captured.  The query fails on the default stream while
+// another stream is: `s` itself is not, then.
 bool capturing(hipStream_t s)
 {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
     (void)hipGetLastError();
-    return true;
+    return false;
 }
 
 void free_plan(fdbb_batch_plan *p)
@@ -1529,8 +1529,10 @@ int fdbb_batch_plan_update(fdbb_batch_plan *plan, const fdbb_task *tasks, int nt
     if (rc) return rc;
     // A captured upload runs when its graph is replayed: until then the device
     // table is another list's, so such a plan keeps to the general launch.
-    if (capturing((hipStream_t)stream)) plan->general_only = true;
-    return upload(plan, (hipStream_t)stream);
+    const bool captured = capturing((hipStream_t)stream);
+    rc = upload(plan, (hipStream_t)stream);
+    if (rc == FDBB_OK && captured) plan->general_only = true;
+    return rc;
 }
 
 int fdbb_batch_exec(fdbb_batch_plan *plan, void *stream, int use_graph)

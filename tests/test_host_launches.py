@@ -86,3 +86,27 @@ h.run(plan, s, 1)
 (l,) = h.launches()
 assert not l.replay and l.units > replayed.units
 """)
+
+
+def test_a_failed_capture_query_leaves_the_plan_alone(run):
+    """The query fails on the default stream while another thread captures:
+    that is no capture of this stream.  Neither it nor an upload that fails
+    under a capture takes the list's own launch from the plan for good."""
+    run("""
+s = h.stream()
+tasks = [task(FUSED, 3, 1000)]
+plan = h.plan(tasks)
+h.run(plan, s, 0)
+(own,) = h.launches()
+assert "k_batch_fused" in own.kernel
+h.fail("hipStreamIsCapturing")
+assert h.update(plan, tasks, s) == 0
+h.fail("hipStreamIsCapturing", False)
+h.run(plan, s, 0)
+assert str(h.launches()[0]) == str(own)
+h.fail("hipMemcpyAsync")
+h.capture(s, lambda: h.update(plan, tasks, s))
+h.fail("hipMemcpyAsync", False)
+h.run(plan, s, 0)
+assert str(h.launches()[0]) == str(own)
+""")
