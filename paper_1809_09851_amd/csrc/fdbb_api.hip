@@ -1103,20 +1103,25 @@ struct BatchLaunch {
     }
 };
 
+// A task list as the host knows it.
+struct TaskList {
+    int ntasks = 0;
+    int64_t points = 0;
+    int64_t tiles = 0;  // of the creation shape
+    BatchLaunch launch;  // its own
+};
+
 // The plan's table: the layout above with its prefix sums in tiles of the
 // creation shape, which the general launch reads, behind a second header and
 // second prefix sums (cap + 1) in units of the current list's own launch.
 struct fdbb_batch_plan {
     int device = 0;
     int capacity = 0;
-    int ntasks = 0;
     bool installed = false;     // block == 0 at creation: the installed configurations
     bool general_only = false;  // a list was uploaded inside a capture (see fdbb_batch_plan_update)
     BatchLaunch base;           // as created; base.lds is the staging a task list may need
-    BatchLaunch cur;            // the current task list's own launch
+    TaskList cur;               // the last one uploaded
     BatchLaunch captured;       // what `exec` launches with
-    int64_t points = 0;
-    int64_t tiles = 0;          // of the creation shape
     unsigned char *dev = nullptr;   // task table, capacity `capacity`
     unsigned char *host = nullptr;  // pinned staging copy of the same layout
     size_t bytes = 0;
@@ -1304,7 +1309,7 @@ int fill_table(const fdbb_task *tasks, int ntasks, int cap, int block, int ppt, 
 }
 
 // Validate tasks and fill the plan's pinned staging copy.
-int stage_tasks(fdbb_batch_plan *p, const fdbb_task *tasks, int ntasks)
+int stage_tasks(fdbb_batch_plan *p, const fdbb_task *tasks, int ntasks, TaskList *next)
 {
     if (ntasks < 0 || ntasks > p->capacity) return fail(FDBB_EINVAL, "ntasks exceeds the plan capacity");
     if (ntasks > 0 && !tasks) return fail(FDBB_EINVAL, "tasks must not be NULL");
@@ -1330,21 +1335,40 @@ int stage_tasks(fdbb_batch_plan *p, const fdbb_task *tasks, int ntasks)
         if (e != hipSuccess) return fail_hip(e, "hipEventSynchronize");
     }
     std::memcpy(p->host, tmp.data(), used);
-    p->ntasks = ntasks;
-    p->tiles = info.tiles;
-    p->points = info.points;
-    p->cur = l;
+    *next = TaskList{ntasks, info.points, info.tiles, l};
     return FDBB_OK;
 }
 
-int upload(fdbb_batch_plan *p, hipStream_t s)
+// Whether `s` is being captured.  The query fails on the default stream while
+// another stream is: `s` itself is not, then.
+bool capturing(hipStream_t s)
 {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return false;
+}
+
+// Uploads the staged list, which becomes the plan's once the copy is queued:
+// after a copy that failed, the table is still the one that the list before
+// launches over.
+int upload(fdbb_batch_plan *p, const TaskList &next, hipStream_t s)
+{
+    // A captured upload runs when its graph is replayed: until then the device
+    // table is another list's, so such a plan keeps to the general launch.
+    const bool captured = capturing(s);
     // header, prefix sums and the tasks in use (not the whole capacity)
-    const size_t used = p->units_bytes() + table_task_offset(p->capacity) + (size_t)p->ntasks * sizeof(TaskDev);
+    const size_t used = p->units_bytes() + table_task_offset(p->capacity) + (size_t)next.ntasks * sizeof(TaskDev);
     hipError_t e = hipMemcpyAsync(p->dev, p->host, used, hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return fail_hip(e, "hipMemcpyAsync");
+    p->cur = next;
+    if (captured) p->general_only = true;
     e = hipEventRecord(p->uploaded, s);
-    if (e != hipSuccess) return fail_hip(e, "hipEventRecord");
+    if (e != hipSuccess) {
+        // nothing else keeps the next list from the staging copy
+        (void)hipStreamSynchronize(s);
+        return fail_hip(e, "hipEventRecord");
+    }
     return FDBB_OK;
 }
 
@@ -1372,7 +1396,7 @@ int launch_list(fdbb_batch_plan *p, hipStream_t s)
     const int64_t *prefix = p->unit_prefix(p->dev);
     const int64_t *header = p->unit_header(p->dev);
     void *args[] = {&tasks, &prefix, &header};
-    const BatchLaunch &l = p->cur;
+    const BatchLaunch &l = p->cur.launch;
     hipError_t e = hipLaunchKernel(l.kernel, dim3((unsigned)l.grid), dim3((unsigned)l.block), args, l.lds, s);
     if (e != hipSuccess) return fail_hip(e, "batch kernel launch");
     return FDBB_OK;
@@ -1402,16 +1426,6 @@ int capture(hipGraphExec_t *exec, F launch)
     }
     if (graph) (void)hipGraphDestroy(graph);
     return rc;
-}
-
-// Whether `s` is being captured.  The query fails on the default stream while
-// another stream is: `s` itself is not, then.
-bool capturing(hipStream_t s)
-{
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
-    (void)hipGetLastError();
-    return false;
 }
 
 void free_plan(fdbb_batch_plan *p)
@@ -1496,7 +1510,8 @@ int fdbb_batch_plan_create(const fdbb_task *tasks, int ntasks, int capacity, int
         free_plan(p);
         return fail_hip(e, "hipEventCreate");
     }
-    if ((rc = stage_tasks(p, tasks, ntasks))) {
+    TaskList first;
+    if ((rc = stage_tasks(p, tasks, ntasks, &first))) {
         const std::string msg = g_last_error;
         free_plan(p);
         return fail(rc, msg);
@@ -1506,11 +1521,12 @@ int fdbb_batch_plan_create(const fdbb_task *tasks, int ntasks, int capacity, int
         free_plan(p);
         return fail_hip(e, "hipMemcpy");
     }
+    p->cur = first;
     // Capture the list's own launch: it is replayed for every list that wants
     // the same one (only the device table that the kernel reads changes).
     if (ntasks > 0) {
         rc = capture(&p->exec, [&](hipStream_t cs) { return launch_list(p, cs); });
-        p->captured = p->cur;
+        p->captured = p->cur.launch;
     }
     if (rc) {
         const std::string msg = g_last_error;
@@ -1525,14 +1541,9 @@ int fdbb_batch_plan_update(fdbb_batch_plan *plan, const fdbb_task *tasks, int nt
 {
     g_last_error.clear();
     if (!plan) return fail(FDBB_EINVAL, "plan must not be NULL");
-    int rc = stage_tasks(plan, tasks, ntasks);
-    if (rc) return rc;
-    // A captured upload runs when its graph is replayed: until then the device
-    // table is another list's, so such a plan keeps to the general launch.
-    const bool captured = capturing((hipStream_t)stream);
-    rc = upload(plan, (hipStream_t)stream);
-    if (rc == FDBB_OK && captured) plan->general_only = true;
-    return rc;
+    TaskList next;
+    int rc = stage_tasks(plan, tasks, ntasks, &next);
+    return rc ? rc : upload(plan, next, (hipStream_t)stream);
 }
 
 int fdbb_batch_exec(fdbb_batch_plan *plan, void *stream, int use_graph)
@@ -1544,8 +1555,8 @@ int fdbb_batch_exec(fdbb_batch_plan *plan, void *stream, int use_graph)
     // the general one, launched directly: a graph launch on a stream that is
     // being captured runs at once and leaves nothing in the capture.
     if (plan->general_only || capturing((hipStream_t)stream)) return launch_general(plan, (hipStream_t)stream);
-    if (plan->tiles == 0) return FDBB_OK;
-    if (!use_graph || !plan->exec || !(plan->cur == plan->captured)) return launch_list(plan, (hipStream_t)stream);
+    if (plan->cur.tiles == 0) return FDBB_OK;
+    if (!use_graph || !plan->exec || !(plan->cur.launch == plan->captured)) return launch_list(plan, (hipStream_t)stream);
     hipError_t e = hipGraphLaunch(plan->exec, (hipStream_t)stream);
     return e == hipSuccess ? FDBB_OK : fail_hip(e, "hipGraphLaunch");
 }
@@ -1613,8 +1624,8 @@ int fdbb_batch_plan_config(const fdbb_batch_plan *plan, int *block, int *ppt, in
 int fdbb_batch_plan_info(const fdbb_batch_plan *plan, int64_t *points, int64_t *tiles)
 {
     if (!plan) return fail(FDBB_EINVAL, "plan must not be NULL");
-    if (points) *points = plan->points;
-    if (tiles) *tiles = plan->tiles;
+    if (points) *points = plan->cur.points;
+    if (tiles) *tiles = plan->cur.tiles;
     return FDBB_OK;
 }
 

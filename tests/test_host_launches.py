@@ -110,3 +110,26 @@ h.fail("hipMemcpyAsync", False)
 h.run(plan, s, 0)
 assert str(h.launches()[0]) == str(own)
 """)
+
+
+def test_a_failed_upload_leaves_the_list_that_was(run):
+    """The table on the device is unchanged, so the launch still is the one
+    that reads it, and what the plan reports too."""
+    run("""
+s = h.stream()
+plan = h.plan([task(FUSED, 3, 1000), task(FLUX, 2, 70)], block=256)
+h.run(plan, s, 0)
+(own,) = h.launches()
+for failing in ("hipMemcpyAsync", "hipEventRecord"):
+    h.fail(failing)
+    assert h.update(plan, [task(FUSED, 3, 5000)], s) == EHIP
+    h.fail(failing, False)
+    h.run(plan, s, 0)
+    (l,) = h.launches()
+    points, tiles = ctypes.c_int64(), ctypes.c_int64()
+    h.lib.fdbb_batch_plan_info(plan, ctypes.byref(points), ctypes.byref(tiles))
+    if failing == "hipMemcpyAsync":
+        assert str(l) == str(own) and (points.value, tiles.value) == (1070, 5), l
+    else:  # the table has arrived
+        assert "k_batch_fused" in l.kernel and (points.value, tiles.value) == (5000, 20), l
+""")
