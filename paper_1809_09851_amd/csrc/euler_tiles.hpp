@@ -40,8 +40,9 @@ struct Args {
     Gas gas;
 };
 
-// W values at a global address that is aligned to one value only: a packed
-// (fields, n) tensor with an odd n or a view that starts inside a row has no
+// N consecutive values: `reg` in registers and in LDS, where every staged run
+// starts on 16 bytes, and `mem` at a global address that is aligned to one
+// value only.  A packed (fields, n) tensor with an odd n or a view that starts inside a row has no
 // 16-byte-aligned rows.  gfx950's multi-dword global accesses ask for dword
 // alignment alone, so such rows take the same wide accesses as aligned ones.
 // Element-wise accesses for them (lane stride W values) cost 2D flux FP32 on
@@ -50,11 +51,15 @@ struct Args {
 // FP64 and 1288 against 287 us in FP32.  Packed inputs with aligned outputs
 // run as fast as aligned ones; what is left with packed outputs is the cache
 // lines shared by two runs.
+// A plain typedef, dereferenced as such: an alias template and a deduced or
+// explicit template argument both drop the alignment.
 template <typename T, int N>
-using vec_t = T __attribute__((ext_vector_type(N), aligned(sizeof(T))));
-// The same values in LDS, where every staged run starts on 16 bytes.
-template <typename T, int N>
-using lds_vec_t = T __attribute__((ext_vector_type(N)));
+struct Run {
+    typedef T reg __attribute__((ext_vector_type(N)));
+    typedef reg mem __attribute__((aligned(alignof(T))));
+};
+static_assert(alignof(Run<float, 4>::mem) == 4 && alignof(Run<double, 2>::mem) == 8, "one value's alignment");
+static_assert(alignof(Run<float, 4>::reg) == 16 && alignof(Run<double, 2>::reg) == 16, "16-byte LDS reads");
 
 // Points per chunk and chunks per thread.  A chunk is the unit of one
 // vector access and of the FP64 per-point state held in registers at one
@@ -73,8 +78,16 @@ struct Chunk {
 // average, products with L or R) load with nt: timed alternately in one
 // process on the same buffers, that made them 5-8 % faster in 3D FP64,
 // while the single-input kernels (flux, fused pass) were 2-3 % slower.
-template <bool NTL, typename V>
-__device__ __forceinline__ V get(const V *p)
+template <bool NTL, typename T, int N>
+__device__ __forceinline__ typename Run<T, N>::reg get(const T *p)
+{
+    const typename Run<T, N>::mem *q = reinterpret_cast<const typename Run<T, N>::mem *>(p);
+    if constexpr (NTL) return __builtin_nontemporal_load(q);
+    else return *q;
+}
+
+template <bool NTL, typename T>
+__device__ __forceinline__ T get(const T *p)
 {
     if constexpr (NTL) return __builtin_nontemporal_load(p);
     else return *p;
@@ -88,7 +101,7 @@ __device__ __forceinline__ void load_chunk(const T *__restrict__ p, int cnt, dou
         if constexpr (W == 1) {
             x[0] = (double)get<NTL, T>(p);
         } else {
-            const vec_t<T, W> v = get<NTL, vec_t<T, W>>(reinterpret_cast<const vec_t<T, W> *>(p));
+            const typename Run<T, W>::reg v = get<NTL, T, W>(p);
 #pragma unroll
             for (int j = 0; j < W; ++j) x[j] = (double)v[j];
         }
@@ -130,22 +143,33 @@ enum : int { kStoreRegular = 0, kStoreNT = 1, kStoreNTSc1 = 2 };
 // its own wide stores for this, but it cannot see the store inside an asm
 // statement and reuses the registers as soon as the statement ends, so
 // the 16-byte form carries its own s_nop 1 (two wait states).
-template <int NT, typename V>
-__device__ __forceinline__ void put(V *p, V v)
+template <typename T, typename V>
+__device__ __forceinline__ void put_sc1(T *p, V v)
 {
-    if constexpr (NT == kStoreNTSc1) {
-        static_assert(sizeof(V) == 4 || sizeof(V) == 8 || sizeof(V) == 16, "4-, 8- or 16-byte stores");
-        if constexpr (sizeof(V) == 16)
-            asm volatile("global_store_dwordx4 %0, %1, off nt sc1\n\ts_nop 1" : : "v"(p), "v"(v));
-        else if constexpr (sizeof(V) == 8)
-            asm volatile("global_store_dwordx2 %0, %1, off nt sc1" : : "v"(p), "v"(v));
-        else
-            asm volatile("global_store_dword %0, %1, off nt sc1" : : "v"(p), "v"(v));
-    } else if constexpr (NT == kStoreNT) {
-        __builtin_nontemporal_store(v, p);
-    } else {
-        *p = v;
-    }
+    static_assert(sizeof(V) == 4 || sizeof(V) == 8 || sizeof(V) == 16, "4-, 8- or 16-byte stores");
+    if constexpr (sizeof(V) == 16)
+        asm volatile("global_store_dwordx4 %0, %1, off nt sc1\n\ts_nop 1" : : "v"(p), "v"(v));
+    else if constexpr (sizeof(V) == 8)
+        asm volatile("global_store_dwordx2 %0, %1, off nt sc1" : : "v"(p), "v"(v));
+    else
+        asm volatile("global_store_dword %0, %1, off nt sc1" : : "v"(p), "v"(v));
+}
+
+template <int NT, typename T, int N>
+__device__ __forceinline__ void put(T *p, typename Run<T, N>::reg v)
+{
+    typename Run<T, N>::mem *q = reinterpret_cast<typename Run<T, N>::mem *>(p);
+    if constexpr (NT == kStoreNTSc1) put_sc1(p, v);
+    else if constexpr (NT == kStoreNT) __builtin_nontemporal_store(v, q);
+    else *q = v;
+}
+
+template <int NT, typename T>
+__device__ __forceinline__ void put(T *p, T v)
+{
+    if constexpr (NT == kStoreNTSc1) put_sc1(p, v);
+    else if constexpr (NT == kStoreNT) __builtin_nontemporal_store(v, p);
+    else *p = v;
 }
 
 // Store W consecutive FP64 values at p, rounded to T (cnt of them valid).
@@ -156,10 +180,10 @@ __device__ __forceinline__ void store_chunk(T *__restrict__ p, int cnt, const do
         if constexpr (W == 1) {
             put<NT, T>(p, (T)x[0]);
         } else {
-            vec_t<T, W> v;
+            typename Run<T, W>::reg v;
 #pragma unroll
             for (int j = 0; j < W; ++j) v[j] = (T)x[j];
-            put<NT, vec_t<T, W>>(reinterpret_cast<vec_t<T, W> *>(p), v);
+            put<NT, T, W>(p, v);
         }
     } else {
 #pragma unroll
@@ -791,9 +815,8 @@ __device__ __forceinline__ void wave_copy_out(const T *lds, T *dst, int count, i
 {
     constexpr int W = 16 / (int)sizeof(T);
     const int chunks = count / W;
-    const lds_vec_t<T, W> *src = reinterpret_cast<const lds_vec_t<T, W> *>(lds);
-    vec_t<T, W> *out = reinterpret_cast<vec_t<T, W> *>(dst);
-    for (int c = lane; c < chunks; c += kWave) put<NT, vec_t<T, W>>(out + c, src[c]);
+    const typename Run<T, W>::reg *src = reinterpret_cast<const typename Run<T, W>::reg *>(lds);
+    for (int c = lane; c < chunks; c += kWave) put<NT, T, W>(dst + c * W, src[c]);
     for (int e = chunks * W + lane; e < count; e += kWave) put<NT, T>(dst + e, lds[e]);
 }
 
