@@ -4,7 +4,8 @@ Argument marshalling only: every building block runs in the HIP kernels of
 the library.  There is no CPU fallback; if the library is missing, loading
 raises.  Calls on plain device tensors are marshalled by the extension module
 ``_binding`` (csrc/binding.cpp), which answers None for everything else; the
-code here then makes the call, or raises what is wrong with it.
+code here then makes the call, or raises what is wrong with it.  Without the
+module, after a warning, the code here makes every call.
 
 Field sets are 2-D tensors ``(fields, n)`` whose rows are ``ld`` elements
 apart (``ld = t.stride(0) >= n``, unit stride along points), float64 or
@@ -18,6 +19,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 
 import torch
 
@@ -88,12 +90,20 @@ _empty_fields, _empty_blocks = _first("_empty_fields"), _first("_empty_blocks")
 BLOCKS, FLAT = -1, -2  # how a slot of _run lies, next to a number of field rows
 
 
+def _not_native(*args):
+    """In place of the extension module's functions: no case is plain."""
+    return None
+
+
 def _bind(lib):
     global _run, _char_apply, _viscous_flux, _empty_fields, _empty_blocks
     try:
         from . import _binding
-    except ImportError as exc:
-        raise RuntimeError("the native binding is not built; run `python -m paper_1809_09851_amd.build`") from exc
+    except ImportError as exc:  # not built, or against another torch
+        warnings.warn(f"the native binding is not usable ({exc}): calls take about 4 us more on the host; "
+                      "run `python -m paper_1809_09851_amd.build`", RuntimeWarning, stacklevel=3)
+        _run = _char_apply = _viscous_flux = _empty_fields = _empty_blocks = _not_native
+        return
     addr = [ctypes.cast(getattr(lib, f), _p).value for f in ("fdbb_task_run", "fdbb_char_apply", "fdbb_viscous_flux")]
     _binding.bind(*addr, torch._C._cuda_getCurrentRawStream)
     _run, _char_apply, _viscous_flux = _binding.run, _binding.char_apply, _binding.viscous_flux
