@@ -209,6 +209,18 @@ PyObject *viscous_flux(PyObject *, PyObject *const *a, Py_ssize_t na)
     END_HANDLE_TH_ERRORS
 }
 
+// Uninitialised values of `shape`, whose second dimension is padded, for u's
+// points, on its device and of its type.  Other Python threads run meanwhile: an allocation that has to
+// give cached blocks back waits for the device.
+at::Tensor empty_like_points(at::DimVector shape, const at::Tensor &u)
+{
+    struct NoGil {
+        PyThreadState *state = PyEval_SaveThread();
+        ~NoGil() { PyEval_RestoreThread(state); }
+    } no_gil;
+    return at::empty(shape, u.options()).narrow(1, 0, u.size(1));
+}
+
 int64_t padded(int64_t n) { return std::max<int64_t>(64, (n + 63) / 64 * 64); }
 
 // empty_fields(fields, U): uninitialised rows for U's points, of its type and
@@ -221,8 +233,7 @@ PyObject *empty_fields(PyObject *, PyObject *const *a, Py_ssize_t na)
     if (!int_of(a[0], &fields) || fields < 0) return not_plain();
     const at::Tensor *u = plain(a[1]);
     if (!u || u->dim() != 2) return not_plain();
-    const int64_t n = u->size(1);
-    return THPVariable_Wrap(at::empty({fields, padded(n)}, u->options()).narrow(1, 0, n));
+    return THPVariable_Wrap(empty_like_points({fields, padded(u->size(1))}, *u));
     END_HANDLE_TH_ERRORS
 }
 
@@ -235,8 +246,8 @@ PyObject *empty_blocks(PyObject *, PyObject *const *a, Py_ssize_t na)
     if (!int_of(a[0], &dim) || dim < 0) return not_plain();
     const at::Tensor *u = plain(a[1]);
     if (!u || u->dim() != 2) return not_plain();
-    const int64_t n = u->size(1), K = dim + 2;
-    return THPVariable_Wrap(at::empty({dim, padded(n), K, K}, u->options()).narrow(1, 0, n));
+    const int64_t K = dim + 2;
+    return THPVariable_Wrap(empty_like_points({dim, padded(u->size(1)), K, K}, *u));
     END_HANDLE_TH_ERRORS
 }
 
