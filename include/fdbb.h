@@ -249,12 +249,12 @@ int fdbb_viscous_flux(int dim, double mu, double kappa, int dtype, const void *U
  * written with streaming stores, 0: regular stores; a streaming store sets
  * the nt cache-policy bit, and in the fused pass, flux Jacobian,
  * eigenvector blocks, flux and Riemann invariants, in FP64 cons2prim and
- * prim2cons and in FP32 |v|^2 also sc1, the device-scope bit).  Large calls of an op that
- * writes a field set at one point per thread without a grid cap take at least
- * 512 threads where the output rows do not start on cache lines, and in the
- * 2D and 3D flux and Riemann invariants regular stores.  Returns
+ * prim2cons and in FP32 |v|^2 also sc1, the device-scope bit).  Returns
  * FDBB_EINVAL for values outside these sets.  The table is process-wide and
- * safe to update while other threads launch. */
+ * safe to update while other threads launch.  A launch may reserve dynamic
+ * LDS on top, which bounds the workgroups resident on a compute unit, and in
+ * large 3D calls that write K x K blocks several workgroups may share a
+ * tile. */
 int fdbb_set_launch_config(int op, int dim, int dtype, int block, int ppt, int grid_cap,
                            int nontemporal);
 int fdbb_get_launch_config(int op, int dim, int dtype, int *block, int *ppt, int *grid_cap,
@@ -272,8 +272,20 @@ int fdbb_set_small_launch_config(int op, int dim, int dtype, int64_t max_n, int 
 /* max_n 0 and the large configuration's values when no entry is set. */
 int fdbb_get_small_launch_config(int op, int dim, int dtype, int64_t *max_n, int *block, int *ppt,
                                  int *grid_cap, int *nontemporal);
+/* The library's own choice, as the binding installs it from the autotuned
+ * table: sets the configuration for calls of at most max_n points as above
+ * (max_n 0: the one for all others).  While the values in force are the ones
+ * last given here (or the built-in defaults), a call of 2^19 or more points
+ * of an op that writes a field set, at one point per thread without a grid
+ * cap, takes at least 512 threads where the output rows do not start on
+ * cache lines, and in the 2D and 3D flux and Riemann invariants regular
+ * stores.  Other values are launched as they are. */
+int fdbb_install_launch_config(int op, int dim, int dtype, int64_t max_n, int block, int ppt, int grid_cap,
+                               int nontemporal);
+
 /* The configuration a call of n points of (op, dim, dtype) launches with
- * (outputs may be NULL); n < 0 gives FDBB_EINVAL. */
+ * where its output rows start on cache lines (see fdbb_install_launch_config
+ * for other rows; outputs may be NULL); n < 0 gives FDBB_EINVAL. */
 int fdbb_launch_config_for(int op, int dim, int dtype, int64_t n, int *block, int *ppt, int *grid_cap,
                            int *nontemporal);
 

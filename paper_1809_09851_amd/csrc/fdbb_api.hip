@@ -78,9 +78,6 @@ struct Config {
     int nt;
 };
 
-std::atomic<uint64_t> g_cfg[FDBB_NUM_OPS][3][2];
-std::once_flag g_cfg_once;
-
 uint64_t pack(const Config &c)
 {
     return (uint64_t)(uint16_t)c.block | ((uint64_t)(uint8_t)c.ppt << 16) | ((uint64_t)(c.nt ? 1 : 0) << 24) |
@@ -97,6 +94,23 @@ Config unpack(uint64_t v)
     return c;
 }
 
+std::atomic<uint64_t> g_cfg[FDBB_NUM_OPS][3][2];
+std::once_flag g_cfg_once;
+
+// The small-launch entries: calls of n <= g_small_max points take
+// g_small_cfg (no entry while g_small_max is 0).  The setter stores the
+// configuration before the bound and the remover clears the bound first, so
+// a launch that sees a non-zero bound also sees a configuration that was
+// valid for this (op, dim, dtype).
+std::atomic<uint64_t> g_small_cfg[FDBB_NUM_OPS][3][2];
+std::atomic<int64_t> g_small_max[FDBB_NUM_OPS][3][2];
+
+// The library's own choice for both (the defaults above, or the installed
+// table): a launch with these values may be fitted to its rows, one with
+// others is a caller's and stays as it is.
+std::atomic<uint64_t> g_own_cfg[FDBB_NUM_OPS][3][2];
+std::atomic<uint64_t> g_own_small_cfg[FDBB_NUM_OPS][3][2];
+
 void init_configs()
 {
     for (int op = 0; op < FDBB_NUM_OPS; ++op)
@@ -112,6 +126,7 @@ void init_configs()
                 c.grid_cap = 0;
                 c.nt = 1;
                 g_cfg[op][d][t].store(pack(c));
+                g_own_cfg[op][d][t].store(pack(c));
             }
 }
 
@@ -121,19 +136,14 @@ Config get_config(int op, int dim, int dtype)
     return unpack(g_cfg[op][dim - 1][dtype].load(std::memory_order_relaxed));
 }
 
-// The small-launch entries: calls of n <= g_small_max points take
-// g_small_cfg (no entry while g_small_max is 0).  The setter stores the
-// configuration before the bound and the remover clears the bound first, so
-// a launch that sees a non-zero bound also sees a configuration that was
-// valid for this (op, dim, dtype).
-std::atomic<uint64_t> g_small_cfg[FDBB_NUM_OPS][3][2];
-std::atomic<int64_t> g_small_max[FDBB_NUM_OPS][3][2];
-
-Config get_config(int op, int dim, int dtype, int64_t n)
+Config get_config(int op, int dim, int dtype, int64_t n, bool *own = nullptr)
 {
     const int64_t max_n = g_small_max[op][dim - 1][dtype].load(std::memory_order_acquire);
-    if (max_n > 0 && n <= max_n) return unpack(g_small_cfg[op][dim - 1][dtype].load(std::memory_order_relaxed));
-    return get_config(op, dim, dtype);
+    const bool small = max_n > 0 && n <= max_n;
+    const Config c = small ? unpack(g_small_cfg[op][dim - 1][dtype].load(std::memory_order_relaxed))
+                           : get_config(op, dim, dtype);
+    if (own) *own = pack(c) == (small ? g_own_small_cfg : g_own_cfg)[op][dim - 1][dtype].load(std::memory_order_relaxed);
+    return c;
 }
 
 // Launch configuration of the persistent batch kernel, per storage type:
@@ -552,7 +562,9 @@ int launch(Call &c, void *stream)
     int rc = check_alias(c);
     if (rc) return rc;
 
-    const Config cfg = fit_rows(c, get_config(c.op, c.dim, c.dtype, c.a.n));
+    bool own = false;
+    Config cfg = get_config(c.op, c.dim, c.dtype, c.a.n, &own);
+    if (own) cfg = fit_rows(c, cfg);
     const void *fn = kernel_for(c.op, c.dim, c.dtype, cfg.ppt, cfg.nt != 0);
     if (!fn) return fail(FDBB_EINVAL, "no kernel for this configuration");
     DeviceInfo dev;
@@ -1010,6 +1022,17 @@ int fdbb_set_small_launch_config(int op, int dim, int dtype, int64_t max_n, int 
     g_small_cfg[op][dim - 1][dtype].store(pack(Config{block, ppt, grid_cap, nontemporal}), std::memory_order_relaxed);
     g_small_max[op][dim - 1][dtype].store(max_n, std::memory_order_release);
     return FDBB_OK;
+}
+
+int fdbb_install_launch_config(int op, int dim, int dtype, int64_t max_n, int block, int ppt, int grid_cap,
+                               int nontemporal)
+{
+    const int rc = max_n == 0 ? fdbb_set_launch_config(op, dim, dtype, block, ppt, grid_cap, nontemporal)
+                              : fdbb_set_small_launch_config(op, dim, dtype, max_n, block, ppt, grid_cap, nontemporal);
+    if (rc == FDBB_OK)
+        (max_n == 0 ? g_own_cfg : g_own_small_cfg)[op][dim - 1][dtype].store(
+            pack(Config{block, ppt, grid_cap, nontemporal}), std::memory_order_relaxed);
+    return rc;
 }
 
 int fdbb_get_small_launch_config(int op, int dim, int dtype, int64_t *max_n, int *block, int *ppt, int *grid_cap,

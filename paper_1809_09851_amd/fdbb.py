@@ -137,6 +137,7 @@ def library():
         lib.fdbb_get_launch_config.argtypes = [_i, _i, _i, ctypes.POINTER(_i), ctypes.POINTER(_i),
                                                ctypes.POINTER(_i), ctypes.POINTER(_i)]
         lib.fdbb_set_small_launch_config.argtypes = [_i, _i, _i, _i64, _i, _i, _i, _i]
+        lib.fdbb_install_launch_config.argtypes = [_i, _i, _i, _i64, _i, _i, _i, _i]
         lib.fdbb_get_small_launch_config.argtypes = [_i, _i, _i, ctypes.POINTER(_i64)] + [ctypes.POINTER(_i)] * 4
         lib.fdbb_launch_config_for.argtypes = [_i, _i, _i, _i64] + [ctypes.POINTER(_i)] * 4
         lib.fdbb_kernel_info.argtypes = [_i, _i, _i, _i, _i, ctypes.POINTER(_i), ctypes.POINTER(_i)]
@@ -501,6 +502,13 @@ def fdbb_set_small_launch_config(op, dim, dtype, max_n, block=256, ppt=1, grid_c
     check(library().fdbb_set_small_launch_config(op, dim, dtype, max_n, block, ppt, grid_cap, nontemporal))
 
 
+def fdbb_install_launch_config(op, dim, dtype, max_n, block, ppt, grid_cap=0, nontemporal=1):
+    """The library's own choice for calls of at most max_n points (0: for all
+    others), which launches may fit to their rows."""
+    op = OPS[op] if isinstance(op, str) else op
+    check(library().fdbb_install_launch_config(op, dim, dtype, max_n, block, ppt, grid_cap, nontemporal))
+
+
 def fdbb_get_small_launch_config(op, dim, dtype):
     """(max_n, block, ppt, grid_cap, nontemporal); max_n 0 when none is set."""
     op = OPS[op] if isinstance(op, str) else op
@@ -512,7 +520,8 @@ def fdbb_get_small_launch_config(op, dim, dtype):
 
 
 def fdbb_launch_config_for(op, dim, dtype, n):
-    """(block, ppt, grid_cap, nontemporal) a call of n points launches with."""
+    """(block, ppt, grid_cap, nontemporal) a call of n points launches with
+    where its output rows start on cache lines."""
     op = OPS[op] if isinstance(op, str) else op
     b, p, g, t = _i(), _i(), _i(), _i()
     check(library().fdbb_launch_config_for(op, dim, dtype, n, ctypes.byref(b), ctypes.byref(p),

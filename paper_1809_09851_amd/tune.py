@@ -431,8 +431,8 @@ def apply_table(path: str = DEFAULT_TABLE, key: str | None = None) -> int:
                 continue
             if parts[0] == "small" and len(parts) == 4:
                 _, op, dim, dt = parts
-                F.fdbb_set_small_launch_config(op, int(dim), DT[dt][0], e["max_n"], e["block"], e["ppt"],
-                                               e["grid_cap"], e["nt"])
+                install = F.fdbb_install_launch_config if e["max_n"] else F.fdbb_set_small_launch_config  # 0 removes
+                install(op, int(dim), DT[dt][0], e["max_n"], e["block"], e["ppt"], e["grid_cap"], e["nt"])
                 count += 1
                 continue
             op, dim, dt = parts
@@ -440,7 +440,7 @@ def apply_table(path: str = DEFAULT_TABLE, key: str | None = None) -> int:
             if op == "batch":
                 F.fdbb_set_batch_config(code, e["block"], e["ppt"], e["grid_per_cu"], e["nt"])
             else:
-                F.fdbb_set_launch_config(op, int(dim), code, e["block"], e["ppt"], e["grid_cap"], e["nt"])
+                F.fdbb_install_launch_config(op, int(dim), code, 0, e["block"], e["ppt"], e["grid_cap"], e["nt"])
         except (F.FdbbError, KeyError, ValueError) as exc:  # an entry this library does not take
             print(f"fdbb: ignoring tuned entry {name}: {exc}", file=sys.stderr)
             continue

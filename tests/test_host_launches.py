@@ -133,3 +133,33 @@ for failing in ("hipMemcpyAsync", "hipEventRecord"):
     else:  # the table has arrived
         assert "k_batch_fused" in l.kernel and (points.value, tiles.value) == (5000, 20), l
 """)
+
+
+def test_a_callers_configuration_is_launched_as_it_is(run):
+    """Rows that start inside cache lines change the library's own choice of
+    shape and store mode, not the one a caller set."""
+    run("""
+n = (1 << 20) + 1
+U, F = address(5, n), address(15, n)
+def launch():
+    assert h.lib.fdbb_flux(3, ctypes.c_double(1.4), F64, ctypes.c_void_p(U), ctypes.c_int64(n), ctypes.c_void_p(F),
+                           ctypes.c_int64(n), ctypes.c_int64(n), None) == 0
+    (l,) = h.launches()
+    return l.block, "Li0EEEv" in l.kernel  # regular stores
+small = lambda f, *a: f(FLUX, 3, F64, ctypes.c_int64(1 << 21), *a)
+assert h.lib.fdbb_install_launch_config(FLUX, 3, F64, ctypes.c_int64(0), 256, 1, 0, 1) == 0
+assert launch() == (512, True)
+assert h.lib.fdbb_set_launch_config(FLUX, 3, F64, 128, 1, 0, 1) == 0
+assert launch() == (128, False)
+assert small(h.lib.fdbb_install_launch_config, 64, 1, 0, 1) == 0
+assert launch() == (512, True)
+assert small(h.lib.fdbb_set_small_launch_config, 128, 1, 0, 1) == 0
+assert launch() == (128, False)
+assert small(h.lib.fdbb_set_small_launch_config, 64, 1, 0, 1) == 0   # the library's own again
+assert launch() == (512, True)
+assert h.lib.fdbb_set_small_launch_config(FLUX, 3, F64, ctypes.c_int64(0), 0, 0, 0, 0) == 0
+assert launch() == (128, False)
+assert h.lib.fdbb_set_launch_config(FLUX, 3, F64, 256, 1, 0, 1) == 0
+assert launch() == (512, True)
+assert small(h.lib.fdbb_install_launch_config, 100, 1, 0, 1) == EINVAL
+""")
