@@ -391,13 +391,18 @@ constexpr int64_t kApartMaxBytes = (int64_t)512 << 20;
 constexpr int64_t kLastLevelBytes = (int64_t)256 << 20;
 enum { kWhole = 0, kByDirection = 1, kFieldsApart = 2 };
 
-SplitPlan split_of(const Call &c, int64_t tile_pts)
+// Only for one point per thread without a grid cap: more points per thread
+// write as much per workgroup as a bounded set should, and lose by the split
+// (3D FP64 Jacobian at 128 x 4 threads x points 1.14-1.17).
+bool one_point(const Config &cfg) { return cfg.ppt == 1 && cfg.grid_cap == 0; }
+
+SplitPlan split_of(const Call &c, const Config &cfg)
 {
     const int D = c.dim, K = D + 2;
     const int es = (int)elem_size(c.dtype);
     SplitPlan p;
     Split &sp = p.dev;
-    sp.span = (uint32_t)std::max<int64_t>(1, kSpanPoints / tile_pts);
+    sp.span = (uint32_t)std::max<int64_t>(1, kSpanPoints / ((int64_t)cfg.block * cfg.ppt));
     const auto add = [&](uint32_t mask, int values) {
         sp.mask[sp.groups++] = mask;
         p.written = std::max(p.written, values * es);
@@ -407,7 +412,7 @@ SplitPlan split_of(const Call &c, int64_t tile_pts)
         mode = kWhole;
     const int64_t block_bytes = (int64_t)(c.op == FDBB_OP_EIGENVECTORS ? 2 : 1) * D * K * K * es * c.a.n;
     p.cached = block_bytes <= kLastLevelBytes;
-    if (p.cached) mode = kWhole;
+    if (p.cached || !one_point(cfg)) mode = kWhole;
     p.split = mode != kWhole;
     if (c.op == FDBB_OP_EIGENVECTORS) {
         sp.groups = 0;
@@ -456,25 +461,35 @@ SplitPlan split_of(const Call &c, int64_t tile_pts)
 // 8 waves 0.89, 24 waves 0.99).  A whole tile at one point per thread takes
 // 3072 B in 2D FP64 (fused pass 8 waves 0.93, 16 waves 1.00), 2048 B in 1D
 // FP64 (16 waves 0.95, 24 waves 0.97, 12 waves 1.01) and 6208 B in FP32 (3D
-// beyond 512 MiB: 16 waves 0.93-1.00); more points per thread keep what their LDS
-// leaves, and so do blocks that stay in the last-level cache.
+// beyond 512 MiB: 16 waves 0.93-1.00); blocks that stay in the last-level
+// cache keep every wave.
+//
+// Rows are bounded where a call writes 192 MiB or more, three quarters of the
+// last-level cache: smaller calls drain into it, and few waves then cost more
+// at the ramp and the tail than they save (time with the bound over that
+// without, 3D flux FP64: 300 007 points 1.03, 1.5 M 1.08, 1.9 M 1.03, 2.5 M
+// 0.91; 2D viscous flux FP64: 300 007 1.06, 1.2 M 1.02, 3 M 0.97).  More than
+// one point per thread has fewer and heavier waves to begin with and keeps
+// them all: 2D viscous flux FP32 at 4 points each took 1.4 times as long with
+// the bound, 1D cons2prim FP64 of 1 000 003 points at 4 each 1.16 times.
 constexpr int kMaxWaves = 32, kMinWaves = 8;
 constexpr int kWrittenPerLane = 900;
+constexpr int64_t kBoundedBytes = (int64_t)192 << 20;
 
-int resident_waves(const SplitPlan &p, int dim, int dtype, int ppt)
+int resident_waves(const SplitPlan &p, const Call &c, const Config &cfg)
 {
+    if (!one_point(cfg)) return kMaxWaves;
     if (p.blocks) {
         int per_lane = 1536;
         if (!p.split) {
-            if (ppt > 1 || p.cached) return kMaxWaves;
-            per_lane = dtype == FDBB_F32 ? 6208 : dim == 1 ? 2048 : 3072;
+            if (p.cached) return kMaxWaves;
+            per_lane = c.dtype == FDBB_F32 ? 6208 : c.dim == 1 ? 2048 : 3072;
         }
-        const int waves = std::max(1, per_lane / (p.written * ppt));
-        return std::min(kMaxWaves, waves);
+        return std::min(kMaxWaves, std::max(1, per_lane / p.written));
     }
-    const int per_lane = p.written * ppt;
-    const int waves = std::max(kMinWaves / ppt, (kWrittenPerLane + per_lane / 2) / per_lane);
-    return waves >= kMaxWaves - 4 ? kMaxWaves : std::max(1, waves);
+    if (p.written * c.a.n < kBoundedBytes) return kMaxWaves;
+    const int waves = std::max(kMinWaves, (kWrittenPerLane + p.written / 2) / p.written);
+    return waves >= kMaxWaves - 4 ? kMaxWaves : waves;
 }
 
 // Dynamic LDS that keeps at most about `waves` waves in workgroups of
@@ -572,9 +587,9 @@ int launch(Call &c, void *stream)
     if (rc) return rc;
     const int64_t tile_pts = (int64_t)cfg.block * cfg.ppt;
     int64_t ntiles = (c.a.n + tile_pts - 1) / tile_pts;
-    SplitPlan sp = split_of(c, tile_pts);
+    SplitPlan sp = split_of(c, cfg);
     size_t lds = sp.blocks ? lds_bytes(c.op, c.dim, c.dtype, cfg.block, cfg.ppt) : 0;
-    lds = std::max(lds, residency_lds(resident_waves(sp, c.dim, c.dtype, cfg.ppt), cfg.block, sp.blocks, dev));
+    lds = std::max(lds, residency_lds(resident_waves(sp, c, cfg), cfg.block, sp.blocks, dev));
     rc = set_lds_attr(fn, lds, dev);
     if (rc) return rc;
 

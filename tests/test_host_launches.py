@@ -163,3 +163,50 @@ assert h.lib.fdbb_set_launch_config(FLUX, 3, F64, 256, 1, 0, 1) == 0
 assert launch() == (512, True)
 assert small(h.lib.fdbb_install_launch_config, 100, 1, 0, 1) == EINVAL
 """)
+
+
+CALLS = """
+def fused(dtype, n, dim=3):
+    t = task(FUSED, dim, n, dtype)
+    assert h.lib.fdbb_task_run(ctypes.byref(t), None) == 0
+    (l,) = h.launches()
+    return l
+def flux(dtype, n, dim=3):
+    t = task(FLUX, dim, n, dtype)
+    assert h.lib.fdbb_task_run(ctypes.byref(t), None) == 0
+    (l,) = h.launches()
+    return l
+def shape(op, dim, dtype, *cfg):
+    assert h.lib.fdbb_set_launch_config(op, dim, dtype, *cfg) == 0
+    h.lib.fdbb_set_small_launch_config(op, dim, dtype, ctypes.c_int64(0), 0, 0, 0, 0)
+"""
+
+
+@pytest.mark.parametrize("dtype,es", (("F64", 8), ("F32", 4)))
+def test_only_one_point_per_thread_is_bounded_or_dealt_apart(run, dtype, es):
+    """Reserved LDS and parts of a tile in workgroups of their own are for
+    uncapped launches of one point per thread; other shapes lose by them."""
+    run(CALLS + f"""
+n = 1 << 20
+for block, ppt, cap in ((128, 2, 0), (64, 4, 0), (128, 1, 2048), (128, 1, 0)):
+    shape(FLUX, 3, {dtype}, block, ppt, cap, 1)
+    shape(FUSED, 3, {dtype}, block, ppt, cap, 1)
+    plain = (ppt, cap) != (1, 0)
+    l = flux({dtype}, 8 * n)
+    assert (l.lds == 0) == plain, l
+    l = fused({dtype}, n)
+    tiles = n // (block * ppt)
+    assert l.grid == (min(tiles, cap or tiles) if plain else tiles * (3 if {es} == 8 else 4)), l
+    assert (l.lds == block * ppt * 25 * {es}) == plain, l
+""")
+
+
+@pytest.mark.parametrize("dim,dtype,es", ((3, "F64", 8), (3, "F32", 4), (2, "F64", 8)))
+def test_rows_are_bounded_past_the_cache_only(run, dim, dtype, es):
+    """A pointwise call reserves LDS where it writes 192 MiB or more."""
+    run(CALLS + f"""
+at = -(-(192 << 20) // ({(dim + 2) * dim} * {es}))
+shape(FLUX, {dim}, {dtype}, 128, 1, 0, 1)
+assert flux({dtype}, at - 1, {dim}).lds == 0
+assert flux({dtype}, at, {dim}).lds > 0
+""")
