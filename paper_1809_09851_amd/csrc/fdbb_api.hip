@@ -1177,6 +1177,15 @@ namespace {
 // Whether a task writes K x K blocks.
 bool writes_blocks(const fdbb_task &t) { return t.op == FDBB_OP_FLUX_JACOBIAN || (t.op == FDBB_OP_FUSED && t.out1); }
 
+// LDS that the tasks' blocks are staged in at this shape.
+size_t staged_lds(const fdbb_task *tasks, int ntasks, int block, int ppt)
+{
+    size_t lds = 0;
+    for (int b = 0; b < ntasks; ++b)
+        if (writes_blocks(tasks[b])) lds = std::max(lds, lds_bytes(tasks[b].op, tasks[b].dim, tasks[b].dtype, block, ppt));
+    return lds;
+}
+
 // Sets of parts a block-writing 3D task's tiles are dealt in when they are
 // dealt apart, as split_of deals a single call's.
 int task_groups(const fdbb_task &t)
@@ -1188,9 +1197,15 @@ int task_groups(const fdbb_task &t)
 // Kernel and shape of a task list (valid tasks), timed against one workgroup
 // per tile and the general kernel, on the same buffers.
 //
+// A plan of explicit shape launches the general kernel in it: the rest is for
+// the installed configurations, whose shapes it was timed in (at 64 x 4
+// threads x points, a 3D FP64 list of 6 M points dealt apart took 1.51 times as
+// long as the general kernel, at 128 x 1 with 4 workgroups per compute unit an
+// FP32 one of 1.3 M points 1.53 times).  Parts and bounds also need one point
+// per thread and a grid that leaves the order of units to the hardware.
+//
 // A list of block-writing tasks of one dim and storage type takes the fused
-// batch kernel in the plan's shape (time over the general kernel's at its
-// best shape):
+// batch kernel (time over the general kernel's at its best shape):
 //   3D FP64, parts by direction, 8 waves: 0.89 at 14 M points in 96 tasks,
 //     0.92 at 3 M in 40 (whole tile, 4 waves: 0.95 and 0.94; parts at 4
 //     waves 1.09, 6 waves 1.1, unlimited 0.97); from 32 GiB of blocks the
@@ -1203,20 +1218,21 @@ int task_groups(const fdbb_task &t)
 //   2D whole tile: FP64 8 waves 0.95 (unlimited 1.03), FP32 0.72; 1D 0.78
 //     and 0.53 without a bound (16 waves 0.78 and 0.76);
 //   lists that fit in the last-level cache: the whole tile, no bound and, in
-//     2D and 3D, regular stores under the installed configurations (3D FP64
-//     200 K points 0.93, streaming 1.02; 1D 900 K 0.92 streaming, 1.03
-//     regular).
-// Any other list under the installed configurations takes the general kernel
-// at 128 threads and, unless its grid is smaller, a workgroup per tile: one
-// point per thread where it stages 2D or 3D blocks (48 mixed requests of
-// 733 MB: 0.75 of the fused shape's time; 2 points 0.81), else two (1D and
-// 3D flux FP64 0.92 and 0.84; 1 point 1.3 and 0.90).
+//     2D and 3D, regular stores (3D FP64 200 K points 0.93, streaming 1.02;
+//     1D 900 K 0.92 streaming, 1.03 regular).
+// Any other list takes the general kernel at 128 threads and, unless its grid
+// is smaller, a workgroup per tile: one point per thread where it stages 2D or
+// 3D blocks (48 mixed requests of 733 MB: 0.75 of the fused shape's time; 2
+// points 0.81), else two (1D and 3D flux FP64 0.92 and 0.84; 1 point 1.3 and
+// 0.90).
 constexpr int64_t kListApartMaxBytes = (int64_t)32 << 30;
 
 BatchLaunch pick_launch(const fdbb_task *tasks, int ntasks, const BatchLaunch &base, bool installed,
                         const DeviceInfo &dev)
 {
     BatchLaunch l = base;
+    l.lds = staged_lds(tasks, ntasks, l.block, l.ppt);
+    if (!installed) return l;
     const fdbb_task *first = nullptr;
     bool uniform = true;
     int rows = 0;
@@ -1239,30 +1255,26 @@ BatchLaunch pick_launch(const fdbb_task *tasks, int ntasks, const BatchLaunch &b
             const bool f64 = first->dtype == FDBB_F64;
             const int64_t block_bytes = (int64_t)D * KK * es * points;
             const bool cached = block_bytes + (int64_t)rows * es * points <= kLastLevelBytes;
-            l.parts = D == 3 && !cached && block_bytes <= (f64 ? kListApartMaxBytes : kApartMaxBytes);
+            const bool dealt = l.ppt == 1 && l.grid >= dev.cus * 64;
+            l.parts = D == 3 && dealt && !cached && block_bytes <= (f64 ? kListApartMaxBytes : kApartMaxBytes);
             const int written = es * l.ppt * (!l.parts ? rows + D * KK : f64 ? KK + (rows + D - 1) / D : KK);
             int per_lane = 0;  // bytes that the resident waves write per lane, 0: no bound
             if (l.parts) per_lane = f64 ? 2200 : 0;
-            else if (!cached && D > 1 && l.ppt == 1) per_lane = f64 ? 3072 : 6208;
+            else if (!cached && D > 1 && dealt) per_lane = f64 ? 3072 : 6208;
             const int waves = per_lane ? std::max(1, std::min(kMaxWaves, per_lane / written)) : kMaxWaves;
-            if (installed && cached && D > 1) l.nt = 0, k = kernel_batch_fused(D, first->dtype, l.ppt, l.nt);
+            if (cached && D > 1) l.nt = 0, k = kernel_batch_fused(D, first->dtype, l.ppt, l.nt);
             l.kernel = k;
             l.lds = std::max(lds_bytes(FDBB_OP_FLUX_JACOBIAN, D, first->dtype, l.block, l.ppt),
                              residency_lds(waves, l.block, true, dev));
             return l;
         }
     }
-    if (installed) {
-        bool staged = false;
-        for (int b = 0; b < ntasks; ++b) staged = staged || (writes_blocks(tasks[b]) && tasks[b].dim > 1);
-        l.block = 128, l.ppt = staged ? 1 : 2, l.nt = staged ? 2 : 1;
-        l.grid = dev.cus * 64;
-        l.kernel = kernel_batch(l.ppt, l.nt);
-    }
-    l.lds = 0;
-    for (int b = 0; b < ntasks; ++b)
-        if (writes_blocks(tasks[b]))
-            l.lds = std::max(l.lds, lds_bytes(tasks[b].op, tasks[b].dim, tasks[b].dtype, l.block, l.ppt));
+    bool staged = false;
+    for (int b = 0; b < ntasks; ++b) staged = staged || (writes_blocks(tasks[b]) && tasks[b].dim > 1);
+    l.block = 128, l.ppt = staged ? 1 : 2, l.nt = staged ? 2 : 1;
+    l.grid = dev.cus * 64;
+    l.kernel = kernel_batch(l.ppt, l.nt);
+    l.lds = staged_lds(tasks, ntasks, l.block, l.ppt);
     return l;
 }
 
@@ -1522,12 +1534,9 @@ int fdbb_batch_plan_create(const fdbb_task *tasks, int ntasks, int capacity, int
     (void)hipGetDevice(&p->device);
     // LDS for the largest Jacobian staging among the first task list; a plan
     // created empty reserves enough for any task (3D FP64 blocks).
-    size_t lds = ntasks == 0 ? lds_bytes(FDBB_OP_FLUX_JACOBIAN, 3, FDBB_F64, block, ppt) : 0;
-    for (int b = 0; b < ntasks; ++b)
-        if (writes_blocks(tasks[b]))
-            lds = std::max(lds, lds_bytes(tasks[b].op, tasks[b].dim, tasks[b].dtype, block, ppt));
-    p->base.lds = lds;
-    if ((rc = set_lds_attr(p->base.kernel, lds, dev))) {
+    p->base.lds = ntasks == 0 ? lds_bytes(FDBB_OP_FLUX_JACOBIAN, 3, FDBB_F64, block, ppt)
+                              : staged_lds(tasks, ntasks, block, ppt);
+    if ((rc = set_lds_attr(p->base.kernel, p->base.lds, dev))) {
         free_plan(p);
         return rc;
     }

@@ -299,14 +299,17 @@ def search_batch(dt: str, reps: int = 5, space=None, verbose=False, nblocks: int
     code, dtype = DT[dt]
     es = 8 if dt == "f64" else 4
     tasks, points, keep = batch_workload(dtype, nblocks)
-    cus = torch.cuda.get_device_properties(torch.cuda.current_device()).multi_processor_count
+    old = F.fdbb_get_batch_config(code)
     space = space or list(itertools.product(BATCH_BLOCKS, BATCH_PPTS, BATCH_GRID_PER_CU, BATCH_STORE_MODES))
     results = []
     for block, ppt, gpc, nt in space:
         if block * ppt * 25 * es > 160 * 1024:  # 3D Jacobian staging must fit in LDS
             continue
         try:
-            plan = B.Plan(tasks, block=block, ppt=ppt, grid=cus * gpc, nontemporal=nt)
+            # through the installed configuration, which chooses kernel and
+            # parts by the list; a plan of explicit shape does not
+            F.fdbb_set_batch_config(code, block, ppt, gpc, nt)
+            plan = B.Plan(tasks)
         except F.FdbbError:
             continue
         ms = time_launch(lambda: plan.run(graph=True), reps)
@@ -315,8 +318,7 @@ def search_batch(dt: str, reps: int = 5, space=None, verbose=False, nblocks: int
         if verbose:
             print(f"  batch {dt} cfg={(block, ppt, gpc, nt)} {ms:.4f} ms", file=sys.stderr, flush=True)
     results.sort()
-    if results:
-        F.fdbb_set_batch_config(code, *results[0][1])
+    F.fdbb_set_batch_config(code, *(results[0][1] if results else old))
     del keep, tasks
     torch.cuda.empty_cache()
     return results, points

@@ -117,7 +117,7 @@ def test_a_failed_upload_leaves_the_list_that_was(run):
     that reads it, and what the plan reports too."""
     run("""
 s = h.stream()
-plan = h.plan([task(FUSED, 3, 1000), task(FLUX, 2, 70)], block=256)
+plan = h.plan([task(FUSED, 3, 1000), task(FLUX, 2, 70)])
 h.run(plan, s, 0)
 (own,) = h.launches()
 for failing in ("hipMemcpyAsync", "hipEventRecord"):
@@ -209,4 +209,21 @@ at = -(-(192 << 20) // ({(dim + 2) * dim} * {es}))
 shape(FLUX, {dim}, {dtype}, 128, 1, 0, 1)
 assert flux({dtype}, at - 1, {dim}).lds == 0
 assert flux({dtype}, at, {dim}).lds > 0
+""")
+
+
+@pytest.mark.parametrize("listed", ("[task(FUSED, 3, 1 << 20)]", "[task(JACOBIAN, 2, 300, F32), task(FUSED, 2, 9, F32)]",
+                                    "[task(FUSED, 3, 1000), task(FLUX, 2, 70)]"))
+@pytest.mark.parametrize("block,ppt,grid,nt", ((256, 1, 0, 1), (64, 4, 0, 2), (128, 1, 1024, 0), (64, 8, 5, 1)))
+def test_a_plan_of_explicit_shape_launches_in_it(run, listed, block, ppt, grid, nt):
+    """The kernels and bounds of installed configurations are for these."""
+    run(f"""
+s = h.stream()
+tasks = {listed}
+plan = h.plan(tasks, block={block}, ppt={ppt}, grid={grid}, nt={nt})
+h.run(plan, s, 0)
+(l,) = h.launches()
+assert "7k_batchILi{ppt}ELi{nt}E" in l.kernel and l.block == {block}, l
+assert l.grid == min({grid} or 256 * (2048 // {block}), l.units)
+assert l.lds == max({block} * {ppt} * (t.dim + 2) ** 2 * (4 if t.dtype == F32 else 8) for t in tasks if t.op != FLUX)
 """)
