@@ -225,5 +225,6 @@ h.run(plan, s, 0)
 (l,) = h.launches()
 assert "7k_batchILi{ppt}ELi{nt}E" in l.kernel and l.block == {block}, l
 assert l.grid == min({grid} or 256 * (2048 // {block}), l.units)
-assert l.lds == max({block} * {ppt} * (t.dim + 2) ** 2 * (4 if t.dtype == F32 else 8) for t in tasks if t.op != FLUX)
+staged = max({block} * {ppt} * (t.dim + 2) ** 2 * (4 if t.dtype == F32 else 8) for t in tasks if t.op != FLUX)
+assert l.lds == (max(staged, 163840 * {block} // 512) if {ppt} == 1 else staged)
 """)
