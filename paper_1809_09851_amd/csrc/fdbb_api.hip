@@ -443,6 +443,59 @@ SplitPlan split_of(const Call &c, const Config &cfg)
     return p;
 }
 
+// Output rows that start inside a cache line (packed tensors of odd length,
+// offset views) split a line between every two workgroups, which usually run
+// on different XCDs and each write their part of it to memory.  Longer runs
+// leave fewer such lines: the pointwise ops that write a field set take at
+// least 512 threads at one point each (time over the table's shape, mean over
+// dims, types and packed sets of 1 to 12 M points: characteristic product
+// 0.89, Roe average and adjoint 0.90, viscous flux and characteristic
+// transforms 0.94); the transforms only where the table gives a thread one
+// point (1D cons2char at 2 and 4 points: 1.09 and 1.28).  The streaming stores
+// of the flux and the Riemann invariants carry sc1, which writes parts of
+// lines through at once; in 2D and 3D regular stores, which L2 merges, are
+// faster then (flux 0.77, 0.91, 0.64, 0.81 for 2D FP32, FP64, 3D FP32, FP64;
+// invariants 0.87, 0.96, 0.81, 0.92; 1D 0.98 to 1.13, left alone).  Below 2^19
+// points or 8 MiB of output the rows stay in cache and nothing changes (1D
+// FP32 characteristic product of 600 011 points 1.08); one direction's flux
+// needs 24 MiB (3D FP32: 600 011 points 1.11, 1 000 003 1.05, 2 500 009 0.89).
+constexpr int64_t kLineBytes = 128;
+constexpr int64_t kRaggedMin = (int64_t)1 << 19;
+constexpr int64_t kRaggedBytes = (int64_t)8 << 20, kRaggedDirBytes = (int64_t)24 << 20;
+constexpr int kRaggedBlock = 512;
+
+bool ragged_rows(const Call &c)
+{
+    const uintptr_t starts = (uintptr_t)c.a.out0 | (uintptr_t)(c.a.ld_out0 * (int64_t)elem_size(c.dtype));
+    return c.a.n >= kRaggedMin && starts % kLineBytes != 0;
+}
+
+Config fit_rows(const Call &c, Config cfg)
+{
+    const int64_t bytes = written_values(c.op, c.dim) * (int64_t)elem_size(c.dtype) * c.a.n;
+    if (!ragged_rows(c) || bytes < (c.op == FDBB_OP_FLUX_DIR ? kRaggedDirBytes : kRaggedBytes)) return cfg;
+    switch (family_of(c.op)) {
+    case kFamFlux:
+    case kFamRiemann:
+        if (c.dim == 1) return cfg;
+        cfg.nt = 0;
+        break;
+    case kFamCons2Char:
+    case kFamChar2Cons:
+        if (cfg.ppt != 1) return cfg;
+        break;
+    case kFamAdjoint:
+    case kFamCharApply:
+    case kFamRoe:
+    case kFamViscous: break;
+    default: return cfg;
+    }
+    cfg.block = std::max(cfg.block, kRaggedBlock);
+    cfg.ppt = 1;
+    cfg.grid_cap = 0;
+    return cfg;
+}
+
 // Waves that may be resident on a compute unit.  A wave writes as many rows
 // as its op has output fields, far apart in memory, so every resident wave
 // adds that many open DRAM rows; past about 57 KB of output in flight per
@@ -468,13 +521,15 @@ SplitPlan split_of(const Call &c, const Config &cfg)
 // last-level cache: smaller calls drain into it, and few waves then cost more
 // at the ramp and the tail than they save (time with the bound over that
 // without, 3D flux FP64: 300 007 points 1.03, 1.5 M 1.08, 1.9 M 1.03, 2.5 M
-// 0.91; 2D viscous flux FP64: 300 007 1.06, 1.2 M 1.02, 3 M 0.97).  More than
-// one point per thread has fewer and heavier waves to begin with and keeps
-// them all: 2D viscous flux FP32 at 4 points each took 1.4 times as long with
-// the bound, 1D cons2prim FP64 of 1 000 003 points at 4 each 1.16 times.
+// 0.91; 2D viscous flux FP64: 300 007 1.06, 1.2 M 1.02, 3 M 0.97).  Rows that
+// start inside cache lines are bounded from 48 MiB (2D viscous flux FP64, 1 M
+// and 2.5 M points 0.96 and 0.92, 600 011 1.02; 3D flux FP64 600 011 0.94).
+// More than one point per thread has fewer and heavier waves to begin with and
+// keeps them all: 2D viscous flux FP32 at 4 points each took 1.4 times as long
+// with the bound, 1D cons2prim FP64 of 1 000 003 points at 4 each 1.16 times.
 constexpr int kMaxWaves = 32, kMinWaves = 8;
 constexpr int kWrittenPerLane = 900;
-constexpr int64_t kBoundedBytes = (int64_t)192 << 20;
+constexpr int64_t kBoundedBytes = (int64_t)192 << 20, kRaggedBoundedBytes = (int64_t)48 << 20;
 
 int resident_waves(const SplitPlan &p, const Call &c, const Config &cfg)
 {
@@ -487,7 +542,7 @@ int resident_waves(const SplitPlan &p, const Call &c, const Config &cfg)
         }
         return std::min(kMaxWaves, std::max(1, per_lane / p.written));
     }
-    if (p.written * c.a.n < kBoundedBytes) return kMaxWaves;
+    if (p.written * c.a.n < (ragged_rows(c) ? kRaggedBoundedBytes : kBoundedBytes)) return kMaxWaves;
     const int waves = std::max(kMinWaves, (kWrittenPerLane + p.written / 2) / p.written);
     return waves >= kMaxWaves - 4 ? kMaxWaves : waves;
 }
@@ -530,45 +585,6 @@ int set_lds_attr(const void *fn, size_t lds, const DeviceInfo &dev)
         // another kernel took this slot meanwhile: keep probing
     }
     return FDBB_OK;  // table full (more kernels than exist): the limit is raised anyway
-}
-
-// Output rows that start inside a cache line (packed tensors of odd length,
-// offset views) split a line between every two workgroups, which usually run
-// on different XCDs and each write their part of it to memory.  Longer runs
-// leave fewer such lines: the pointwise ops that write a field set take at
-// least 512 threads (time over the table's shape, mean over dims, types and
-// packed sets of 1 to 12 M points: characteristic product 0.89, Roe average
-// and adjoint 0.90, viscous flux and characteristic transforms 0.94).  The
-// streaming stores of the flux and the Riemann invariants carry sc1, which
-// writes parts of lines through at once; in 2D and 3D regular stores, which
-// L2 merges, are faster then (flux 0.77, 0.91, 0.64, 0.81 for 2D FP32, FP64,
-// 3D FP32, FP64; invariants 0.87, 0.96, 0.81, 0.92; 1D 0.98 to 1.13, left
-// alone).  Below 2^19 points the rows stay in cache and nothing changes.
-constexpr int64_t kLineBytes = 128;
-constexpr int64_t kRaggedMin = (int64_t)1 << 19;
-constexpr int kRaggedBlock = 512;
-
-Config fit_rows(const Call &c, Config cfg)
-{
-    if (c.a.n < kRaggedMin || cfg.ppt != 1 || cfg.grid_cap != 0 || cfg.block >= kRaggedBlock) return cfg;
-    const uintptr_t starts = (uintptr_t)c.a.out0 | (uintptr_t)(c.a.ld_out0 * (int64_t)elem_size(c.dtype));
-    if (starts % kLineBytes == 0) return cfg;
-    switch (family_of(c.op)) {
-    case kFamFlux:
-    case kFamRiemann:
-        if (c.dim == 1) return cfg;
-        cfg.nt = 0;
-        break;
-    case kFamAdjoint:
-    case kFamCharApply:
-    case kFamRoe:
-    case kFamViscous:
-    case kFamCons2Char:
-    case kFamChar2Cons: break;
-    default: return cfg;
-    }
-    cfg.block = kRaggedBlock;
-    return cfg;
 }
 
 int launch(Call &c, void *stream)

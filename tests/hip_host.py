@@ -9,7 +9,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIBRARY = os.path.join(os.path.dirname(HERE), "paper_1809_09851_amd", "libfdbb.so")
 EINVAL, EHIP = 1, 4
-CONS2PRIM, FLUX, JACOBIAN, FUSED = 0, 3, 4, 8
+CONS2PRIM, FLUX, JACOBIAN, CONS2CHAR, FUSED, FLUX_DIR = 0, 3, 4, 6, 8, 16
 F64, F32 = 0, 1
 
 
@@ -34,7 +34,7 @@ def task(op, dim, n, dtype=F64):
     K, es = dim + 2, 4 if dtype == F32 else 8
     t = Task(op=op, dim=dim, dtype=dtype, gamma=1.4, n=n)
     t.in0, t.ld_in0 = address(K, n, es=es), n
-    rows = {CONS2PRIM: K, FLUX: K * dim, FUSED: K * dim}.get(op)
+    rows = {CONS2PRIM: K, CONS2CHAR: K, FLUX_DIR: K, FLUX: K * dim, FUSED: K * dim}.get(op)
     if rows:
         t.out0, t.ld_out0 = address(rows, n, es=es), n
     if op == JACOBIAN:

@@ -202,13 +202,21 @@ for block, ppt, cap in ((128, 2, 0), (64, 4, 0), (128, 1, 2048), (128, 1, 0)):
 
 
 @pytest.mark.parametrize("dim,dtype,es", ((3, "F64", 8), (3, "F32", 4), (2, "F64", 8)))
-def test_rows_are_bounded_past_the_cache_only(run, dim, dtype, es):
-    """A pointwise call reserves LDS where it writes 192 MiB or more."""
+@pytest.mark.parametrize("mib,ragged", ((192, 0), (48, 1)))
+def test_rows_are_bounded_past_the_cache_only(run, dim, dtype, es, mib, ragged):
+    """A pointwise call reserves LDS where it writes 192 MiB or more, 48 MiB
+    where its rows start inside cache lines."""
     run(CALLS + f"""
-at = -(-(192 << 20) // ({(dim + 2) * dim} * {es}))
+per = {(dim + 2) * dim} * {es}
+at = max(-(-({mib} << 20) // per), 1 << 19)  # rows below 2^19 points count as whole lines
 shape(FLUX, {dim}, {dtype}, 128, 1, 0, 1)
-assert flux({dtype}, at - 1, {dim}).lds == 0
-assert flux({dtype}, at, {dim}).lds > 0
+if {ragged}:
+    below, above = (at - 1) | 1, at | 1
+    below -= 2 * (below >= at)
+else:
+    below, above = at // 32 * 32 - 32, at + -at % 32
+assert flux({dtype}, below, {dim}).lds == 0
+assert flux({dtype}, above, {dim}).lds > 0
 """)
 
 
@@ -227,4 +235,28 @@ assert "7k_batchILi{ppt}ELi{nt}E" in l.kernel and l.block == {block}, l
 assert l.grid == min({grid} or 256 * (2048 // {block}), l.units)
 staged = max({block} * {ppt} * (t.dim + 2) ** 2 * (4 if t.dtype == F32 else 8) for t in tasks if t.op != FLUX)
 assert l.lds == (max(staged, 163840 * {block} // 512) if {ppt} == 1 else staged)
+""")
+
+
+def test_rows_inside_cache_lines_take_long_runs(run):
+    """Whatever shape the library would take for whole lines: one point per
+    thread, 512 threads, regular stores for the flux; the characteristic
+    transforms at several points per thread and small outputs stay."""
+    run("""
+def shape(op, dim, n, dtype):
+    t = task(op, dim, n, dtype)
+    assert h.lib.fdbb_task_run(ctypes.byref(t), None) == 0
+    (l,) = h.launches()
+    return l.block, l.kernel
+def same(l, block, ppt, nt=None):
+    assert l[0] == block and f"Li{ppt}ELi" in l[1], l
+    assert nt is None or f"Li{nt}EEEv" in l[1], l
+same(shape(FLUX, 3, 1 << 20, F64), 256, 2)
+same(shape(FLUX, 3, (1 << 20) + 1, F64), 512, 1, 0)
+same(shape(FLUX, 3, (1 << 20) + 1, F32), 512, 1, 0)
+same(shape(FLUX, 3, (1 << 19) - 1, F64), 256, 2)
+same(shape(FLUX, 1, (1 << 20) + 1, F32), 256, 4)
+same(shape(FLUX_DIR, 3, 1000003, F32), 256, 4)
+same(shape(FLUX_DIR, 3, 2500009, F32), 512, 1, 0)
+same(shape(CONS2CHAR, 1, 2500009, F64), 256, 2)
 """)
