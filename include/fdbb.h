@@ -273,15 +273,18 @@ int fdbb_set_small_launch_config(int op, int dim, int dtype, int64_t max_n, int 
 int fdbb_get_small_launch_config(int op, int dim, int dtype, int64_t *max_n, int *block, int *ppt,
                                  int *grid_cap, int *nontemporal);
 /* The library's own choice, as the binding installs it from the autotuned
- * table: sets the configuration for calls of at most max_n points as above
- * (max_n 0: the one for all others).  While the values in force are the ones
- * last given here (or the built-in defaults), a call of 2^19 or more points
- * of an op that writes a field set, at one point per thread without a grid
- * cap, takes at least 512 threads where the output rows do not start on
- * cache lines, and in the 2D and 3D flux and Riemann invariants regular
- * stores.  Other values are launched as they are. */
-int fdbb_install_launch_config(int op, int dim, int dtype, int64_t max_n, int block, int ppt, int grid_cap,
-                               int nontemporal);
+ * table, by size: level 1 sets the small entry above (max_n = bound), level 2
+ * the configuration for all other calls (bound is ignored), and while those
+ * are the values in force, level 0 the one for calls of at most `bound`
+ * points of the small ones, level 3 the one for calls of at least `bound`
+ * points of the others (bound 0 removes the level's entry; level 2 has none).
+ * With its own values (or the built-in defaults) the library may also fit a
+ * call to its rows: where the output rows of 2^19 or more points do not start
+ * on cache lines, ops that write a field set may take one point per thread, at
+ * least 512 threads and no grid cap, and the 2D and 3D flux and Riemann
+ * invariants regular stores.  A caller's values are launched as they are. */
+int fdbb_install_launch_config(int op, int dim, int dtype, int level, int64_t bound, int block, int ppt,
+                               int grid_cap, int nontemporal);
 
 /* The configuration a call of n points of (op, dim, dtype) launches with
  * where its output rows start on cache lines (see fdbb_install_launch_config

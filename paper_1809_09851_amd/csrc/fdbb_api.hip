@@ -105,11 +105,20 @@ std::once_flag g_cfg_once;
 std::atomic<uint64_t> g_small_cfg[FDBB_NUM_OPS][3][2];
 std::atomic<int64_t> g_small_max[FDBB_NUM_OPS][3][2];
 
-// The library's own choice for both (the defaults above, or the installed
+// The library's own choice for both (the defaults below, or the installed
 // table): a launch with these values may be fitted to its rows, one with
 // others is a caller's and stays as it is.
 std::atomic<uint64_t> g_own_cfg[FDBB_NUM_OPS][3][2];
 std::atomic<uint64_t> g_own_small_cfg[FDBB_NUM_OPS][3][2];
+
+// Beside its own small entry the library may have one for fewer points ([0],
+// up to the bound), and beside its own other one one for more ([1], from the
+// bound on); a bound of 0 is none.  No two shapes fit all sizes: waves of one
+// point per thread that just exceed what the chip holds leave it almost empty
+// for the last of them (1D cons2prim FP64, 128 x 1: 1.14 of the best at 2^20
+// points), where shapes of 4 points per thread lose half below 2^17.
+std::atomic<uint64_t> g_level_cfg[2][FDBB_NUM_OPS][3][2];
+std::atomic<int64_t> g_level_bound[2][FDBB_NUM_OPS][3][2];
 
 void init_configs()
 {
@@ -142,8 +151,13 @@ Config get_config(int op, int dim, int dtype, int64_t n, bool *own = nullptr)
     const bool small = max_n > 0 && n <= max_n;
     const Config c = small ? unpack(g_small_cfg[op][dim - 1][dtype].load(std::memory_order_relaxed))
                            : get_config(op, dim, dtype);
-    if (own) *own = pack(c) == (small ? g_own_small_cfg : g_own_cfg)[op][dim - 1][dtype].load(std::memory_order_relaxed);
-    return c;
+    const bool ours = pack(c) == (small ? g_own_small_cfg : g_own_cfg)[op][dim - 1][dtype].load(std::memory_order_relaxed);
+    if (own) *own = ours;
+    if (!ours) return c;
+    const int level = small ? 0 : 1;
+    const int64_t bound = g_level_bound[level][op][dim - 1][dtype].load(std::memory_order_acquire);
+    if (bound == 0 || (small ? n > bound : n < bound)) return c;
+    return unpack(g_level_cfg[level][op][dim - 1][dtype].load(std::memory_order_relaxed));
 }
 
 // Launch configuration of the persistent batch kernel, per storage type:
@@ -1055,15 +1069,30 @@ int fdbb_set_small_launch_config(int op, int dim, int dtype, int64_t max_n, int 
     return FDBB_OK;
 }
 
-int fdbb_install_launch_config(int op, int dim, int dtype, int64_t max_n, int block, int ppt, int grid_cap,
+int fdbb_install_launch_config(int op, int dim, int dtype, int level, int64_t bound, int block, int ppt, int grid_cap,
                                int nontemporal)
 {
-    const int rc = max_n == 0 ? fdbb_set_launch_config(op, dim, dtype, block, ppt, grid_cap, nontemporal)
-                              : fdbb_set_small_launch_config(op, dim, dtype, max_n, block, ppt, grid_cap, nontemporal);
-    if (rc == FDBB_OK)
-        (max_n == 0 ? g_own_cfg : g_own_small_cfg)[op][dim - 1][dtype].store(
-            pack(Config{block, ppt, grid_cap, nontemporal}), std::memory_order_relaxed);
-    return rc;
+    if (level < 0 || level > 3) return fail(FDBB_EINVAL, "level must be 0 to 3");
+    const uint64_t packed = pack(Config{block, ppt, grid_cap, nontemporal});
+    if (level == 1 || level == 2) {
+        const int rc = level == 2 ? fdbb_set_launch_config(op, dim, dtype, block, ppt, grid_cap, nontemporal)
+                                  : fdbb_set_small_launch_config(op, dim, dtype, bound, block, ppt, grid_cap, nontemporal);
+        if (rc == FDBB_OK && (level == 2 || bound > 0))
+            (level == 2 ? g_own_cfg : g_own_small_cfg)[op][dim - 1][dtype].store(packed, std::memory_order_relaxed);
+        return rc;
+    }
+    if (op < 0 || op >= FDBB_NUM_OPS || dim < 1 || dim > 3 || (dtype != FDBB_F64 && dtype != FDBB_F32))
+        return fail(FDBB_EINVAL, "unknown op, dim or dtype");
+    if (bound < 0) return fail(FDBB_EINVAL, "bound must not be negative");
+    if (bound > 0 && !config_ok(block, ppt, grid_cap, nontemporal)) return fail(FDBB_EINVAL, "invalid launch configuration");
+    if (bound > 0 && stages_blocks(op) && block > kMaxBlockStaged)
+        return fail(FDBB_EINVAL, "kernels that stage K x K blocks take at most 256 threads per workgroup");
+    // clear the bound while the configuration changes, then publish both
+    std::atomic<int64_t> &b = g_level_bound[level == 0 ? 0 : 1][op][dim - 1][dtype];
+    b.store(0, std::memory_order_release);
+    g_level_cfg[level == 0 ? 0 : 1][op][dim - 1][dtype].store(packed, std::memory_order_relaxed);
+    b.store(bound, std::memory_order_release);
+    return FDBB_OK;
 }
 
 int fdbb_get_small_launch_config(int op, int dim, int dtype, int64_t *max_n, int *block, int *ppt, int *grid_cap,

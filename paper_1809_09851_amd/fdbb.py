@@ -137,7 +137,7 @@ def library():
         lib.fdbb_get_launch_config.argtypes = [_i, _i, _i, ctypes.POINTER(_i), ctypes.POINTER(_i),
                                                ctypes.POINTER(_i), ctypes.POINTER(_i)]
         lib.fdbb_set_small_launch_config.argtypes = [_i, _i, _i, _i64, _i, _i, _i, _i]
-        lib.fdbb_install_launch_config.argtypes = [_i, _i, _i, _i64, _i, _i, _i, _i]
+        lib.fdbb_install_launch_config.argtypes = [_i, _i, _i, _i, _i64, _i, _i, _i, _i]
         lib.fdbb_get_small_launch_config.argtypes = [_i, _i, _i, ctypes.POINTER(_i64)] + [ctypes.POINTER(_i)] * 4
         lib.fdbb_launch_config_for.argtypes = [_i, _i, _i, _i64] + [ctypes.POINTER(_i)] * 4
         lib.fdbb_kernel_info.argtypes = [_i, _i, _i, _i, _i, ctypes.POINTER(_i), ctypes.POINTER(_i)]
@@ -502,11 +502,12 @@ def fdbb_set_small_launch_config(op, dim, dtype, max_n, block=256, ppt=1, grid_c
     check(library().fdbb_set_small_launch_config(op, dim, dtype, max_n, block, ppt, grid_cap, nontemporal))
 
 
-def fdbb_install_launch_config(op, dim, dtype, max_n, block, ppt, grid_cap=0, nontemporal=1):
-    """The library's own choice for calls of at most max_n points (0: for all
-    others), which launches may fit to their rows."""
+def fdbb_install_launch_config(op, dim, dtype, level, bound, block=256, ppt=1, grid_cap=0, nontemporal=1):
+    """The library's own choice by size: level 1 for calls of at most `bound`
+    points, 2 for all others, 0 for fewer still, 3 from `bound` points on
+    (bound 0 removes an entry); launches may fit it to their rows."""
     op = OPS[op] if isinstance(op, str) else op
-    check(library().fdbb_install_launch_config(op, dim, dtype, max_n, block, ppt, grid_cap, nontemporal))
+    check(library().fdbb_install_launch_config(op, dim, dtype, level, bound, block, ppt, grid_cap, nontemporal))
 
 
 def fdbb_get_small_launch_config(op, dim, dtype):

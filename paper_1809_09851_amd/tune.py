@@ -1,14 +1,19 @@
 """Launch-configuration autotuner.
 
 Searches workgroup size x points per thread x grid cap x store mode for an
-(op, dim, dtype) at a given problem size, timing each candidate with HIP
-events on the launch stream (median of repeated launches), and installs the
-fastest with ``fdbb_set_launch_config``.  Results are kept in a JSON table
+(op, dim, dtype) and installs the winner.  Results are kept in a JSON table
 keyed by device architecture, HIP runtime version and (op, dim, dtype); the
 binding applies the table shipped next to the library when it loads it.
 
-    python -m paper_1809_09851_amd.tune --ops fused,flux_jacobian --dims 3 \\
-        --dtypes f64,f32 --n 16777216 --write paper_1809_09851_amd/tuned_gfx950.json
+    python -m paper_1809_09851_amd.tune --ops fused,flux_jacobian --dims 1,2,3 \\
+        --dtypes f64,f32 --write paper_1809_09851_amd/tuned_gfx950.json
+
+Calls fall into four classes by size (``CLASSES``: up to 3 * 2^17 points, up
+to 2^21, beyond, and from 3 * 2^23 on), each with an entry of its own where one
+pays.  Each shape is timed at every size of the class, odd ones and powers of
+two, in captured graphs over rotating sets of arrays of 1.2 GB in all; ``rank``
+says which is taken.  ``--n N`` tunes the plain entry at N points alone
+instead, by the median of single launches.
 
 The op ``batch`` tunes the persistent batch kernel (block x points per
 thread x workgroups per compute unit x store mode) on the 512-block batched
@@ -18,12 +23,9 @@ explicit configuration, and the request server, use it.
 The op ``serve`` tunes the request server's batch configuration on
 batches packed from the serving request mix (``serve_batch/0/mix``).
 
-``--small N`` tunes the small-launch class instead: each candidate runs
-back to back over rotating copies of an N-point workload (about 1 GB in
-all, so that the last-level cache does not hold them), and a winner more
-than 2 % faster than the large configuration at that size is stored as
-``small/<op>/<dim>/<dtype>`` with max_n = 2N; calls of up to max_n points
-then launch with it (``fdbb_set_small_launch_config``).
+``--small N`` tunes the small-launch class at N points alone: a winner more
+than 2 % faster than the large configuration at that size is stored with
+max_n = 2N (``fdbb_set_small_launch_config``).
 """
 from __future__ import annotations
 
@@ -198,6 +200,140 @@ def time_queued(fns, launches: int = 256, rounds: int = 2) -> float:
     return best
 
 
+# The classes of calls by size, with the level of fdbb_install_launch_config, its
+# bound, the sizes to time and the grid caps to try.  Each gives one entry:
+# tiny/ and small/ with max_n, the plain name, huge/ with min_n.
+CLASSES = {
+    "large": (2, 0, (3000017, 1 << 22, 8000009, 12000017, 1 << 24), (0, 4096, 8192)),
+    "huge": (3, 3 << 23, (33554467, 1 << 26, 100000007), (0, 4096, 8192)),
+    "small": (1, 1 << 21, (600011, 1000003, 1 << 20, 1500001, 1900013), (0, 2048)),
+    "tiny": (0, 3 << 17, (1009, 4099, 20011, 130003, 300007), (0, 2048)),
+}
+BESIDE = {"tiny": "small", "huge": "large"}  # kept where faster than the neighbour's shape
+MIN_GAIN = 0.01
+MAX_BYTES = 12e9       # moved by one launch
+ROTATED_BYTES = 1.2e9  # in the sets of arrays that launches go through in turn
+SCREEN_MARGIN = 1.15
+
+
+def time_graph(fns, launches: int, rounds: int = 4) -> float:
+    """Microseconds per launch of `launches` launches cycling over `fns`,
+    captured in one graph (best of `rounds` replays)."""
+    for f in fns:
+        f()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        for k in range(launches):
+            fns[k % len(fns)]()
+    g.replay()
+    best = float("inf")
+    for _ in range(rounds):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        g.replay()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) / launches * 1e3)
+    return best
+
+
+def rank(times: dict) -> list:
+    """[(mean, worst, shape)] of {shape: [time at each size]}, the one to take
+    first: `mean` is the geometric mean, `worst` the maximum, over the sizes
+    of the time over the best shape's at that size.  Of the shapes whose mean
+    is within 0.5 % of the lowest, the one with the lowest worst case leads."""
+    best = [min(t) for t in zip(*times.values())]
+    rows = []
+    for cfg, t in times.items():
+        r = [x / b for x, b in zip(t, best)]
+        rows.append((math.exp(sum(map(math.log, r)) / len(r)), max(r), cfg))
+    rows.sort()
+    near = [r for r in rows if r[0] <= rows[0][0] * 1.005]
+    lead = min(near, key=lambda r: (r[1], r[0]))
+    return [lead] + [r for r in rows if r is not lead]
+
+
+def search_range(op: str, dim: int, dt: str, cls: str):
+    """Times every shape over the sizes of a class; returns ({shape: [us at each
+    size]}, sizes).  Shapes that are more than SCREEN_MARGIN off the best at
+    both the class's second and its last size are not timed at the others."""
+    code, dtype = DT[dt]
+    bpp = bytes_per_point(op, dim, 8 if dt == "f64" else 4)
+    sizes = [n for n in CLASSES[cls][2] if n * bpp <= MAX_BYTES]
+    if not sizes:
+        return {}, []
+    one_entry(op, dim, code)
+    old = F.fdbb_get_small_launch_config(op, dim, code)
+    shapes = [c for c in itertools.product(BLOCKS, PPTS, CLASSES[cls][3], STORE_MODES)
+              if F.fdbb_kernel_info(op, dim, code, c[1], c[3])[1] == 0]
+    times = {}
+    screens = {sizes[min(1, len(sizes) - 1)], sizes[-1]}
+    try:
+        for n in sorted(sizes, key=lambda n: n not in screens):
+            if n not in screens and screens:
+                best = {m: min(t[m] for t in times.values()) for m in screens}
+                shapes = [c for c in shapes if c in times and
+                          any(times[c][m] <= SCREEN_MARGIN * best[m] for m in screens)]
+                screens = set()
+            sets = max(2, min(64, math.ceil(ROTATED_BYTES / (bpp * n))))
+            fns = [workload(op, dim, dtype, n) for _ in range(sets)]
+            launches = max(sets, min(256, int(1e10 / (bpp * n))))
+            for c in shapes:
+                try:
+                    F.fdbb_set_small_launch_config(op, dim, code, 1 << 30, *c)
+                    times.setdefault(c, {})[n] = time_graph(fns, launches)
+                except F.FdbbError:
+                    continue  # a configuration this kernel cannot take (block size, LDS)
+            del fns
+            torch.cuda.empty_cache()
+    finally:
+        F.fdbb_set_small_launch_config(op, dim, code, *old)
+    return {c: [t[n] for n in sizes] for c, t in times.items() if len(t) == len(sizes)}, sizes
+
+
+def one_entry(op, dim, code):
+    """Lifts the entries beside the small and the large one, so that a shape
+    set for all sizes is what every call takes."""
+    for level in (0, 3):
+        F.fdbb_install_launch_config(op, dim, code, level, 0)
+
+
+def range_entry(times: dict, sizes: list, cls: str, beside: dict | None = None) -> dict | None:
+    """The table's entry of a search_range; None where it would gain no more than
+    MIN_GAIN over the shape of the entry `beside` it."""
+    rows = rank(times)
+    block, ppt, cap, nt = rows[0][2]
+    if beside:
+        other = [m for m, _, c in rows if c == tuple(beside[k] for k in ("block", "ppt", "grid_cap", "nt"))]
+        if other and other[0] <= rows[0][0] * (1 + MIN_GAIN):
+            return None
+    e = {"block": block, "ppt": ppt, "grid_cap": cap, "nt": nt, "sizes": list(sizes),
+         "us": [round(t, 2) for t in times[rows[0][2]]],
+         "top5": [[round(m, 4), round(w, 4), list(c)] for m, w, c in rows[:5]]}
+    level, bound = CLASSES[cls][:2]
+    if level != 2:
+        e["min_n" if level == 3 else "max_n"] = bound
+    return e
+
+
+def tune_range(op: str, dim: int, dt: str, entries: dict) -> None:
+    """Times all classes of (op, dim, dtype) and puts their entries into
+    `entries`."""
+    key = f"{op}/{dim}/{dt}"
+    for cls in CLASSES:
+        name = key if cls == "large" else f"{cls}/{key}"
+        times, sizes = search_range(op, dim, dt, cls)
+        entries.pop(name, None)
+        if not times:
+            continue
+        beside = BESIDE.get(cls)
+        e = range_entry(times, sizes, cls, entries.get(key if beside == "large" else f"{beside}/{key}") if beside else None)
+        if e:
+            entries[name] = e
+        print(json.dumps({name: e}), flush=True)
+
+
 SMALL_GRID_CAPS = (0, 2048)
 SMALL_MIN_GAIN = 0.02
 
@@ -211,6 +347,7 @@ def search_small(op: str, dim: int, dt: str, n: int, verbose=False, target_bytes
     es = 8 if dt == "f64" else 4
     sets = max(1, min(64, math.ceil(target_bytes / (bytes_per_point(op, dim, es) * n))))
     fns = [workload(op, dim, dtype, n) for _ in range(sets)]
+    one_entry(op, dim, code)
     large = F.fdbb_get_launch_config(op, dim, code)
     F.fdbb_set_small_launch_config(op, dim, code, 0)
     large_ms = time_queued(fns)
@@ -244,6 +381,7 @@ def search(op: str, dim: int, dt: str, n: int, reps: int = 7, space=None, verbos
     code, dtype = DT[dt]
     fn = workload(op, dim, dtype, n)
     space = space or list(itertools.product(BLOCKS, PPTS, GRID_CAPS, STORE_MODES))
+    one_entry(op, dim, code)
     old = F.fdbb_get_launch_config(op, dim, code)
     # a small-launch entry covering n would take over every candidate: lift it
     small = F.fdbb_get_small_launch_config(op, dim, code)
@@ -291,37 +429,42 @@ def batch_workload(dtype, nblocks: int = 512, seed: int = 2):
     return tasks, int(sizes.sum()), keep
 
 
-def search_batch(dt: str, reps: int = 5, space=None, verbose=False, nblocks: int = 512):
-    """Time every batch configuration on the batched workload (one
-    persistent graph-captured launch each); returns [(ms, (block, ppt,
-    grid_per_cu, nt))] sorted and installs the fastest for `dt`."""
+BATCH_LISTS = (24, 96, 512)  # blocks of the batched workload
+
+
+def search_batch(dt: str, reps: int = 5, space=None, verbose=False, lists=BATCH_LISTS):
+    """Times every batch configuration on the first blocks of the batched
+    workload (graph-captured launches); returns ({(block, ppt, grid_per_cu,
+    nt): [ms on each list]}, points of each list) and installs the one that
+    `rank` takes."""
     from . import batch as B
     code, dtype = DT[dt]
     es = 8 if dt == "f64" else 4
-    tasks, points, keep = batch_workload(dtype, nblocks)
+    tasks, _, keep = batch_workload(dtype, max(lists))
     old = F.fdbb_get_batch_config(code)
     space = space or list(itertools.product(BATCH_BLOCKS, BATCH_PPTS, BATCH_GRID_PER_CU, BATCH_STORE_MODES))
-    results = []
-    for block, ppt, gpc, nt in space:
-        if block * ppt * 25 * es > 160 * 1024:  # 3D Jacobian staging must fit in LDS
+    times = {}
+    for cfg in space:
+        if cfg[0] * cfg[1] * 25 * es > 160 * 1024:  # 3D Jacobian staging must fit in LDS
             continue
-        try:
-            # through the installed configuration, which chooses kernel and
-            # parts by the list; a plan of explicit shape does not
-            F.fdbb_set_batch_config(code, block, ppt, gpc, nt)
-            plan = B.Plan(tasks)
-        except F.FdbbError:
-            continue
-        ms = time_launch(lambda: plan.run(graph=True), reps)
-        plan.close()
-        results.append((ms, (block, ppt, gpc, nt)))
+        for k in lists:
+            try:
+                # through the installed configuration, which chooses kernel and
+                # parts by the list; a plan of explicit shape does not
+                F.fdbb_set_batch_config(code, *cfg)
+                plan = B.Plan(tasks[:k])
+            except F.FdbbError:
+                times.pop(cfg, None)
+                break
+            times.setdefault(cfg, []).append(time_launch(lambda: plan.run(graph=True), reps))
+            plan.close()
         if verbose:
-            print(f"  batch {dt} cfg={(block, ppt, gpc, nt)} {ms:.4f} ms", file=sys.stderr, flush=True)
-    results.sort()
-    F.fdbb_set_batch_config(code, *(results[0][1] if results else old))
+            print(f"  batch {dt} cfg={cfg} {times.get(cfg)} ms", file=sys.stderr, flush=True)
+    F.fdbb_set_batch_config(code, *(rank(times)[0][2] if times else old))
+    points = [sum(t.n for t in tasks[:k]) for k in lists]
     del keep, tasks
     torch.cuda.empty_cache()
-    return results, points
+    return times, points
 
 
 def serve_workload(batches: int = 24, seed: int = 7, max_batch: int = 64, max_bytes: float = 64e6):
@@ -431,10 +574,10 @@ def apply_table(path: str = DEFAULT_TABLE, key: str | None = None) -> int:
                 F.fdbb_set_server_batch_config(e["block"], e["ppt"], e["grid_per_cu"], e["nt"])
                 count += 1
                 continue
-            if parts[0] == "small" and len(parts) == 4:
-                _, op, dim, dt = parts
-                install = F.fdbb_install_launch_config if e["max_n"] else F.fdbb_set_small_launch_config  # 0 removes
-                install(op, int(dim), DT[dt][0], e["max_n"], e["block"], e["ppt"], e["grid_cap"], e["nt"])
+            if parts[0] in ("tiny", "small", "huge") and len(parts) == 4:
+                cls, op, dim, dt = parts
+                F.fdbb_install_launch_config(op, int(dim), DT[dt][0], CLASSES[cls][0], e["min_n" if cls == "huge" else "max_n"],
+                                             e["block"], e["ppt"], e["grid_cap"], e["nt"])
                 count += 1
                 continue
             op, dim, dt = parts
@@ -442,7 +585,7 @@ def apply_table(path: str = DEFAULT_TABLE, key: str | None = None) -> int:
             if op == "batch":
                 F.fdbb_set_batch_config(code, e["block"], e["ppt"], e["grid_per_cu"], e["nt"])
             else:
-                F.fdbb_install_launch_config(op, int(dim), code, 0, e["block"], e["ppt"], e["grid_cap"], e["nt"])
+                F.fdbb_install_launch_config(op, int(dim), code, 2, 0, e["block"], e["ppt"], e["grid_cap"], e["nt"])
         except (F.FdbbError, KeyError, ValueError) as exc:  # an entry this library does not take
             print(f"fdbb: ignoring tuned entry {name}: {exc}", file=sys.stderr)
             continue
@@ -456,7 +599,7 @@ def main(argv=None):
     ap.add_argument("--dims", default="3")
     ap.add_argument("--dtypes", default="f64,f32")
     ap.add_argument("--n", default="auto",
-                    help="points per launch, or 'auto' for a working set of about 2 GB per op")
+                    help="points per launch, or 'auto' for the sizes of both classes")
     ap.add_argument("--reps", type=int, default=7)
     ap.add_argument("--small", type=int, default=0,
                     help="tune the small-launch class at this many points instead of the large one")
@@ -481,15 +624,14 @@ def main(argv=None):
         if op == "batch":
             # the batched workload is 3D whatever --dims says
             for dt in args.dtypes.split(","):
-                res, points = search_batch(dt, max(3, args.reps - 2), verbose=args.verbose)
-                if not res:
+                times, points = search_batch(dt, max(3, args.reps - 2), verbose=args.verbose)
+                if not times:
                     continue
-                best_ms, (block, ppt, gpc, nt) = res[0]
-                base = [ms for ms, cfg in res if cfg == (256, 1, 8, 1)]
-                entries[f"batch/3/{dt}"] = {"block": block, "ppt": ppt, "grid_per_cu": gpc, "nt": nt,
-                                            "ms": round(best_ms, 5), "n": points,
-                                            "default_ms": round(base[0], 5) if base else None,
-                                            "top5": [[round(ms, 5), list(c)] for ms, c in res[:5]]}
+                rows = rank(times)
+                block, ppt, gpc, nt = rows[0][2]
+                entries[f"batch/3/{dt}"] = {"block": block, "ppt": ppt, "grid_per_cu": gpc, "nt": nt, "n": points,
+                                            "ms": [round(t, 4) for t in times[rows[0][2]]],
+                                            "top5": [[round(m, 4), round(w, 4), list(c)] for m, w, c in rows[:5]]}
                 print(json.dumps({f"batch/3/{dt}": entries[f"batch/3/{dt}"]}), flush=True)
             continue
         for dim in (int(d) for d in args.dims.split(",")):
@@ -507,7 +649,10 @@ def main(argv=None):
                         entries.pop(name, None)
                     print(json.dumps({name: entries.get(name, {"kept_large": True, **info})}), flush=True)
                     continue
-                n = (auto_size(op, dim, 8 if dt == "f64" else 4) if args.n == "auto" else int(args.n))
+                if args.n == "auto":
+                    tune_range(op, dim, dt, entries)
+                    continue
+                n = int(args.n)
                 res = search(op, dim, dt, n, args.reps, verbose=args.verbose)
                 if not res:
                     print(f"fdbb: no usable configuration for {op}/{dim}/{dt} (all spill or are refused)",

@@ -146,22 +146,23 @@ def launch():
                            ctypes.c_int64(n), ctypes.c_int64(n), None) == 0
     (l,) = h.launches()
     return l.block, "Li0EEEv" in l.kernel  # regular stores
-small = lambda f, *a: f(FLUX, 3, F64, ctypes.c_int64(1 << 21), *a)
-assert h.lib.fdbb_install_launch_config(FLUX, 3, F64, ctypes.c_int64(0), 256, 1, 0, 1) == 0
+small = lambda *a: h.lib.fdbb_set_small_launch_config(FLUX, 3, F64, ctypes.c_int64(1 << 21), *a)
+install = lambda level, bound, *a: h.lib.fdbb_install_launch_config(FLUX, 3, F64, level, ctypes.c_int64(bound), *a)
+assert install(2, 0, 256, 1, 0, 1) == 0
 assert launch() == (512, True)
 assert h.lib.fdbb_set_launch_config(FLUX, 3, F64, 128, 1, 0, 1) == 0
 assert launch() == (128, False)
-assert small(h.lib.fdbb_install_launch_config, 64, 1, 0, 1) == 0
+assert install(1, 1 << 21, 64, 1, 0, 1) == 0
 assert launch() == (512, True)
-assert small(h.lib.fdbb_set_small_launch_config, 128, 1, 0, 1) == 0
+assert small(128, 1, 0, 1) == 0
 assert launch() == (128, False)
-assert small(h.lib.fdbb_set_small_launch_config, 64, 1, 0, 1) == 0   # the library's own again
+assert small(64, 1, 0, 1) == 0   # the library's own again
 assert launch() == (512, True)
 assert h.lib.fdbb_set_small_launch_config(FLUX, 3, F64, ctypes.c_int64(0), 0, 0, 0, 0) == 0
 assert launch() == (128, False)
 assert h.lib.fdbb_set_launch_config(FLUX, 3, F64, 256, 1, 0, 1) == 0
 assert launch() == (512, True)
-assert small(h.lib.fdbb_install_launch_config, 100, 1, 0, 1) == EINVAL
+assert install(1, 1 << 21, 100, 1, 0, 1) == EINVAL
 """)
 
 
@@ -259,4 +260,34 @@ same(shape(FLUX, 1, (1 << 20) + 1, F32), 256, 4)
 same(shape(FLUX_DIR, 3, 1000003, F32), 256, 4)
 same(shape(FLUX_DIR, 3, 2500009, F32), 512, 1, 0)
 same(shape(CONS2CHAR, 1, 2500009, F64), 256, 2)
+""")
+
+
+def test_own_choice_by_size(run):
+    """The library's own entries for fewer and for more points apply beside
+    its own other two, and not where a caller set one of those."""
+    run("""
+I64 = ctypes.c_int64
+install = lambda level, bound, *a: h.lib.fdbb_install_launch_config(FLUX, 2, F64, level, I64(bound), *a)
+def at(n):
+    v = [ctypes.c_int() for _ in range(4)]
+    assert h.lib.fdbb_launch_config_for(FLUX, 2, F64, I64(n), *map(ctypes.byref, v)) == 0
+    return tuple(x.value for x in v)
+cfg = [(64, 1, 0, 1), (128, 1, 0, 1), (256, 2, 0, 1), (512, 4, 0, 0)]
+bound = [1000, 5000, 0, 20000]
+for level in range(4):
+    assert install(level, bound[level], *cfg[level]) == 0
+sizes = (0, 1000, 1001, 5000, 5001, 19999, 20000, 1 << 30)
+assert [cfg.index(at(n)) for n in sizes] == [0, 0, 1, 1, 2, 2, 3, 3]
+h.lib.fdbb_set_small_launch_config(FLUX, 2, F64, I64(5000), 64, 2, 0, 1)
+assert at(1) == at(1001) == (64, 2, 0, 1) and at(20000) == cfg[3]
+h.lib.fdbb_set_launch_config(FLUX, 2, F64, 64, 4, 0, 1)
+assert at(5001) == at(20000) == (64, 4, 0, 1)
+h.lib.fdbb_set_small_launch_config(FLUX, 2, F64, I64(5000), *cfg[1])
+h.lib.fdbb_set_launch_config(FLUX, 2, F64, *cfg[2])
+assert [cfg.index(at(n)) for n in sizes] == [0, 0, 1, 1, 2, 2, 3, 3]
+assert install(0, 0, 0, 0, 0, 0) == 0 and install(3, 0, 0, 0, 0, 0) == 0
+assert [cfg.index(at(n)) for n in sizes] == [1, 1, 1, 1, 2, 2, 2, 2]
+assert install(0, 10, 100, 1, 0, 1) == install(4, 10, 64, 1, 0, 1) == install(3, -1, 64, 1, 0, 1) == EINVAL
+assert h.lib.fdbb_install_launch_config(FUSED, 2, F64, 0, I64(10), 512, 1, 0, 1) == EINVAL
 """)
