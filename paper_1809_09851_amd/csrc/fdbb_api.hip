@@ -393,7 +393,9 @@ struct SplitPlan {
 //     4 and 1.21 over 12 in turn (whole tile 0.96, 0.97, 0.93), at 8 M 0.86
 //     over one and 1.24 over 4 (0.99, 0.99); up to 512 MiB of blocks even 12
 //     sets gain (0.93), beyond the whole tile is taken.  Eigenvector blocks
-//     keep their split (0.85-0.89 over three sets at every size);
+//     keep their split up to 6 GiB: over one, two and four sets 0.87, 0.96 and
+//     0.90 at 7 M points (whole tile 1.00, 0.97, 0.91), 0.89, 0.93 and 0.99 at
+//     12 M (0.98, 0.91, 0.92), 1.00, 0.99 and 1.04 at 2^24 (0.89, 0.89, 0.93);
 //   1D and 2D (K*K a power of two or 9): the whole tile, a split gained
 //     nothing (2D FP64 0.92 against 0.93, 2D FP32 1.02 against 1.00);
 //   blocks that fit in the 256 MB last-level cache: the whole tile (200 003
@@ -401,7 +403,7 @@ struct SplitPlan {
 // Spans of 131072 points: 32768 is level in FP64 (0.933 against 0.930 over 16
 // buffers), 10-20 % slower in FP32; one span over the whole call reads the
 // state from HBM again (2^24 FP64: 1.05).
-constexpr int64_t kApartMaxBytes = (int64_t)512 << 20;
+constexpr int64_t kApartMaxBytes = (int64_t)512 << 20, kEigenApartMaxBytes = (int64_t)6 << 30;
 constexpr int64_t kLastLevelBytes = (int64_t)256 << 20;
 enum { kWhole = 0, kByDirection = 1, kFieldsApart = 2 };
 
@@ -422,9 +424,9 @@ SplitPlan split_of(const Call &c, const Config &cfg)
         p.written = std::max(p.written, values * es);
     };
     int mode = D < 3 ? kWhole : c.dtype == FDBB_F64 ? kByDirection : kFieldsApart;
-    if (D == 3 && family_of(c.op) == kFamFused && c.dtype == FDBB_F32 && (int64_t)D * K * K * es * c.a.n > kApartMaxBytes)
-        mode = kWhole;
-    const int64_t block_bytes = (int64_t)(c.op == FDBB_OP_EIGENVECTORS ? 2 : 1) * D * K * K * es * c.a.n;
+    const bool eigen = c.op == FDBB_OP_EIGENVECTORS;
+    const int64_t block_bytes = (int64_t)(eigen ? 2 : 1) * D * K * K * es * c.a.n;
+    if (c.dtype == FDBB_F32 && block_bytes > (eigen ? kEigenApartMaxBytes : kApartMaxBytes)) mode = kWhole;
     p.cached = block_bytes <= kLastLevelBytes;
     if (p.cached || !one_point(cfg)) mode = kWhole;
     p.split = mode != kWhole;

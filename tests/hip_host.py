@@ -9,7 +9,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIBRARY = os.path.join(os.path.dirname(HERE), "paper_1809_09851_amd", "libfdbb.so")
 EINVAL, EHIP = 1, 4
-CONS2PRIM, FLUX, JACOBIAN, CONS2CHAR, FUSED, FLUX_DIR = 0, 3, 4, 6, 8, 16
+CONS2PRIM, FLUX, JACOBIAN, CONS2CHAR, FUSED, EIGEN, FLUX_DIR = 0, 3, 4, 6, 8, 11, 16
 F64, F32 = 0, 1
 
 
@@ -39,6 +39,9 @@ def task(op, dim, n, dtype=F64):
         t.out0, t.ld_out0 = address(rows, n, es=es), n
     if op == JACOBIAN:
         t.out0, t.ld_out0 = address(dim, n, K * K, es), n
+    if op == EIGEN:
+        t.out0, t.ld_out0 = address(dim, n, K * K, es), n
+        t.out1, t.ld_out1 = address(dim, n, K * K, es), n
     if op == FUSED:
         t.out1, t.ld_out1 = address(dim, n, K * K, es), n
         t.out2, t.ld_out2 = address(2 * dim + 1, n, es=es), n

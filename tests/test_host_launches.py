@@ -291,3 +291,19 @@ assert [cfg.index(at(n)) for n in sizes] == [1, 1, 1, 1, 2, 2, 2, 2]
 assert install(0, 10, 100, 1, 0, 1) == install(4, 10, 64, 1, 0, 1) == install(3, -1, 64, 1, 0, 1) == EINVAL
 assert h.lib.fdbb_install_launch_config(FUSED, 2, F64, 0, I64(10), 512, 1, 0, 1) == EINVAL
 """)
+
+
+@pytest.mark.parametrize("op,mib,blocks,parts", (("FUSED", 512, 3, 4), ("JACOBIAN", 512, 3, 3), ("EIGEN", 6144, 6, 6)))
+def test_fp32_parts_apart_up_to_a_bound(run, op, mib, blocks, parts):
+    """3D FP32 tiles are dealt apart past the last-level cache and up to this
+    much of blocks."""
+    run(CALLS + f"""
+per = {blocks} * 25 * 4
+shape({op}, 3, F32, 256, 1, 0, 1)
+for bound, expected in ((256 << 20, (1, {parts})), ({mib} << 20, ({parts}, 1))):
+    for n, sets in zip((bound // per, bound // per + 1), expected):
+        t = task({op}, 3, n, F32)
+        assert h.lib.fdbb_task_run(ctypes.byref(t), None) == 0
+        (l,) = h.launches()
+        assert l.grid == -(-n // 256) * sets, (n, l)
+""")
