@@ -27,6 +27,10 @@
 #include "../../include/fdbb.h"
 #include "free_list.hpp"
 
+namespace fdbb {
+int task_run_among_others(const fdbb_task &task, void *stream);  // fdbb_api.hip
+}
+
 namespace {
 
 int64_t now_ns()
@@ -228,9 +232,11 @@ int launch(fdbb_server *s, Slot &slot)
     tasks.reserve(slot.batch.size());
     for (const Request &r : slot.batch) tasks.push_back(r.task);
     int rc = FDBB_OK;
-    if (s->mode == FDBB_SERVE_SINGLE || tasks.size() == 1) {
+    if (s->mode == FDBB_SERVE_SINGLE) {
         for (const fdbb_task &t : tasks)
             if ((rc = fdbb_task_run(&t, slot.stream))) break;
+    } else if (tasks.size() == 1) {
+        rc = fdbb::task_run_among_others(tasks[0], slot.stream);
     } else {
         rc = fdbb_batch_plan_update(slot.plan, tasks.data(), (int)tasks.size(), slot.stream);
         if (!rc) rc = fdbb_batch_exec(slot.plan, slot.stream, 0);

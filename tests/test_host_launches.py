@@ -307,3 +307,28 @@ for bound, expected in ((256 << 20, (1, {parts})), ({mib} << 20, ({parts}, 1))):
         (l,) = h.launches()
         assert l.grid == -(-n // 256) * sets, (n, l)
 """)
+
+
+@pytest.mark.parametrize("mode", (0, 1))
+def test_a_server_bounds_waves_on_its_one_stream_only(run, mode):
+    """Slots with streams of their own share the chip: a request that runs
+    alone in one reserves no LDS; the one-stream mode has the chip to itself."""
+    run(CALLS + f"""
+import time
+shape(FLUX, 3, F64, 128, 1, 0, 1)
+server = ctypes.c_void_p()
+assert h.lib.fdbb_server_create(ctypes.c_int64(1 << 30), 2, 8, ctypes.c_double(1e6), {mode}, ctypes.byref(server)) == 0
+h.launches()
+t = task(FLUX, 3, 1 << 21)
+assert h.lib.fdbb_server_submit(server, ctypes.byref(t), ctypes.c_uint64(1)) == 0
+done, count = (ctypes.c_char * 4096)(), ctypes.c_int()
+for _ in range(2000):
+    assert h.lib.fdbb_server_poll(server, done, 8, ctypes.byref(count)) == 0
+    if count.value:
+        break
+    time.sleep(0.002)
+assert count.value == 1
+(l,) = h.launches()
+assert (l.lds > 0) == bool({mode}), l
+h.lib.fdbb_server_destroy(server)
+""")
