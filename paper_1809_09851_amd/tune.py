@@ -11,14 +11,15 @@ binding applies the table shipped next to the library when it loads it.
 Calls fall into four classes by size (``CLASSES``: up to 3 * 2^17 points, up
 to 2^21, beyond, and from 3 * 2^23 on), each with an entry of its own where one
 pays.  Each shape is timed at every size of the class, odd ones and powers of
-two, in captured graphs over rotating sets of arrays of 1.2 GB in all; ``rank``
-says which is taken.  ``--n N`` tunes the plain entry at N points alone
-instead, by the median of single launches.
+two, in captured graphs over rotating sets of arrays of 1.2 GB in all and over
+one set; ``rank`` says which is taken, given the one in the table.  ``--n N``
+tunes the plain entry at N points alone instead, by the median of single
+launches.
 
-The op ``batch`` tunes the persistent batch kernel (block x points per
-thread x workgroups per compute unit x store mode) on the 512-block batched
-workload and stores it as ``batch/3/<dtype>``; plans created without an
-explicit configuration, and the request server, use it.
+The op ``batch`` tunes the batch kernels (block x points per thread x
+workgroups per compute unit x store mode) on three lists of the batched
+workload and stores the result as ``batch/3/<dtype>``; plans created without
+an explicit configuration use it.
 
 The op ``serve`` tunes the request server's batch configuration on
 batches packed from the serving request mix (``serve_batch/0/mix``).
@@ -46,7 +47,7 @@ BLOCKS = (64, 128, 256, 512, 1024)
 PPTS = (1, 2, 4)
 GRID_CAPS = (0, 2048, 4096, 8192)
 STORE_MODES = (1, 0)
-# the persistent batch kernel: block x points per thread x workgroups per
+# the batch kernels: block x points per thread x workgroups per
 # compute unit x store mode (0 regular, 1 nt, 2 nt + sc1)
 BATCH_BLOCKS = (64, 128, 256)
 BATCH_PPTS = (1, 2, 4, 8)
@@ -201,19 +202,19 @@ def time_queued(fns, launches: int = 256, rounds: int = 2) -> float:
 
 
 # The classes of calls by size, with the level of fdbb_install_launch_config, its
-# bound, the sizes to time and the grid caps to try.  Each gives one entry:
-# tiny/ and small/ with max_n, the plain name, huge/ with min_n.
+# bound and the sizes to time.  Each may have an entry: tiny/ and small/ with
+# max_n, the plain name, huge/ with min_n.
 CLASSES = {
-    "large": (2, 0, (3000017, 1 << 22, 8000009, 12000017, 1 << 24), (0, 4096, 8192)),
-    "huge": (3, 3 << 23, (33554467, 1 << 26, 100000007), (0, 4096, 8192)),
-    "small": (1, 1 << 21, (600011, 1000003, 1 << 20, 1500001, 1900013), (0, 2048)),
-    "tiny": (0, 3 << 17, (1009, 4099, 20011, 130003, 300007), (0, 2048)),
+    "large": (2, 0, (3000017, 1 << 22, 8000009, 12000017, 1 << 24)),
+    "huge": (3, 3 << 23, (33554467, 1 << 26, 100000007)),
+    "small": (1, 1 << 21, (600011, 1000003, 1 << 20, 1500001, 1900013)),
+    "tiny": (0, 3 << 17, (1009, 4099, 20011, 130003, 300007)),
 }
-BESIDE = {"tiny": "small", "huge": "large"}  # kept where faster than the neighbour's shape
-MIN_GAIN = 0.01
+BESIDE = {"tiny": "small", "huge": "large"}  # whose shape a class without an entry takes
+KEEP_MARGIN = 0.03  # a shape in force stays unless another is this much faster
 MAX_BYTES = 12e9       # moved by one launch
 ROTATED_BYTES = 1.2e9  # in the sets of arrays that launches go through in turn
-SCREEN_MARGIN = 1.15
+SCREEN_MARGIN = 1.10
 
 
 def time_graph(fns, launches: int, rounds: int = 4) -> float:
@@ -238,26 +239,34 @@ def time_graph(fns, launches: int, rounds: int = 4) -> float:
     return best
 
 
-def rank(times: dict) -> list:
+def rank(times: dict, in_force=None) -> list:
     """[(mean, worst, shape)] of {shape: [time at each size]}, the one to take
     first: `mean` is the geometric mean, `worst` the maximum, over the sizes
-    of the time over the best shape's at that size.  Of the shapes whose mean
-    is within 0.5 % of the lowest, the one with the lowest worst case leads."""
+    of the time over the best shape's at that size.  The shape `in_force` stays
+    if its mean is within KEEP_MARGIN of the lowest: what kernels of other ops
+    leave in the caches moves a shape's time by as much.  Otherwise, of the
+    shapes whose mean is within 0.5 % of the lowest, the one with the lowest
+    worst case leads."""
     best = [min(t) for t in zip(*times.values())]
     rows = []
     for cfg, t in times.items():
         r = [x / b for x, b in zip(t, best)]
         rows.append((math.exp(sum(map(math.log, r)) / len(r)), max(r), cfg))
     rows.sort()
-    near = [r for r in rows if r[0] <= rows[0][0] * 1.005]
+    kept = [r for r in rows if r[2] == in_force and r[0] <= rows[0][0] * (1 + KEEP_MARGIN)]
+    near = kept or [r for r in rows if r[0] <= rows[0][0] * 1.005]
     lead = min(near, key=lambda r: (r[1], r[0]))
     return [lead] + [r for r in rows if r is not lead]
 
 
-def search_range(op: str, dim: int, dt: str, cls: str):
-    """Times every shape over the sizes of a class; returns ({shape: [us at each
-    size]}, sizes).  Shapes that are more than SCREEN_MARGIN off the best at
-    both the class's second and its last size are not timed at the others."""
+def search_range(op: str, dim: int, dt: str, cls: str, in_force=None):
+    """Times every shape over the sizes of a class, over rotating sets of arrays
+    and over one set, part of which stays in the last-level cache as in a step
+    that reads its state again; returns ({shape: [us at each size, rotating,
+    then at each size, one set]}, sizes).  Shapes without a grid cap are tried,
+    since a cap keeps a launch from being dealt in parts or fitted to its rows,
+    and the one in force.  Shapes that are more than SCREEN_MARGIN off the best in all four timings at the class's second and
+    last size are not timed at the others."""
     code, dtype = DT[dt]
     bpp = bytes_per_point(op, dim, 8 if dt == "f64" else 4)
     sizes = [n for n in CLASSES[cls][2] if n * bpp <= MAX_BYTES]
@@ -265,31 +274,36 @@ def search_range(op: str, dim: int, dt: str, cls: str):
         return {}, []
     one_entry(op, dim, code)
     old = F.fdbb_get_small_launch_config(op, dim, code)
-    shapes = [c for c in itertools.product(BLOCKS, PPTS, CLASSES[cls][3], STORE_MODES)
+    shapes = [c for c in itertools.product(BLOCKS, PPTS, (0,), STORE_MODES)
               if F.fdbb_kernel_info(op, dim, code, c[1], c[3])[1] == 0]
+    if in_force and in_force not in shapes:
+        shapes.append(in_force)
     times = {}
     screens = {sizes[min(1, len(sizes) - 1)], sizes[-1]}
+    seen = [(m, w) for m in screens for w in (0, 1)]
     try:
         for n in sorted(sizes, key=lambda n: n not in screens):
-            if n not in screens and screens:
-                best = {m: min(t[m] for t in times.values()) for m in screens}
+            if n not in screens and seen:
+                best = {k: min(t[k] for t in times.values()) for k in seen}
                 shapes = [c for c in shapes if c in times and
-                          any(times[c][m] <= SCREEN_MARGIN * best[m] for m in screens)]
-                screens = set()
+                          (c == in_force or any(times[c][k] <= SCREEN_MARGIN * best[k] for k in seen))]
+                seen = []
             sets = max(2, min(64, math.ceil(ROTATED_BYTES / (bpp * n))))
             fns = [workload(op, dim, dtype, n) for _ in range(sets)]
             launches = max(sets, min(256, int(1e10 / (bpp * n))))
             for c in shapes:
                 try:
                     F.fdbb_set_small_launch_config(op, dim, code, 1 << 30, *c)
-                    times.setdefault(c, {})[n] = time_graph(fns, launches)
+                    t = times.setdefault(c, {})
+                    t[n, 0], t[n, 1] = time_graph(fns, launches), time_graph(fns[:1], launches)
                 except F.FdbbError:
-                    continue  # a configuration this kernel cannot take (block size, LDS)
+                    times.pop(c, None)  # a configuration this kernel cannot take (block size, LDS)
             del fns
             torch.cuda.empty_cache()
     finally:
         F.fdbb_set_small_launch_config(op, dim, code, *old)
-    return {c: [t[n] for n in sizes] for c, t in times.items() if len(t) == len(sizes)}, sizes
+    keys = [(n, w) for w in (0, 1) for n in sizes]
+    return {c: [t[k] for k in keys] for c, t in times.items() if len(t) == len(keys)}, sizes
 
 
 def one_entry(op, dim, code):
@@ -299,15 +313,14 @@ def one_entry(op, dim, code):
         F.fdbb_install_launch_config(op, dim, code, level, 0)
 
 
-def range_entry(times: dict, sizes: list, cls: str, beside: dict | None = None) -> dict | None:
-    """The table's entry of a search_range; None where it would gain no more than
-    MIN_GAIN over the shape of the entry `beside` it."""
-    rows = rank(times)
+def shape_of(entry: dict | None):
+    return tuple(entry[k] for k in ("block", "ppt", "grid_cap", "nt")) if entry else None
+
+
+def range_entry(times: dict, sizes: list, cls: str, in_force=None) -> dict:
+    """The table's entry of a search_range."""
+    rows = rank(times, in_force)
     block, ppt, cap, nt = rows[0][2]
-    if beside:
-        other = [m for m, _, c in rows if c == tuple(beside[k] for k in ("block", "ppt", "grid_cap", "nt"))]
-        if other and other[0] <= rows[0][0] * (1 + MIN_GAIN):
-            return None
     e = {"block": block, "ppt": ppt, "grid_cap": cap, "nt": nt, "sizes": list(sizes),
          "us": [round(t, 2) for t in times[rows[0][2]]],
          "top5": [[round(m, 4), round(w, 4), list(c)] for m, w, c in rows[:5]]}
@@ -319,19 +332,20 @@ def range_entry(times: dict, sizes: list, cls: str, beside: dict | None = None) 
 
 def tune_range(op: str, dim: int, dt: str, entries: dict) -> None:
     """Times all classes of (op, dim, dtype) and puts their entries into
-    `entries`."""
+    `entries`; the tiny and the huge class get none where the neighbour's shape
+    leads."""
     key = f"{op}/{dim}/{dt}"
+    named = lambda cls: key if cls == "large" else f"{cls}/{key}"
     for cls in CLASSES:
-        name = key if cls == "large" else f"{cls}/{key}"
-        times, sizes = search_range(op, dim, dt, cls)
-        entries.pop(name, None)
+        other = shape_of(entries[named(BESIDE[cls])]) if cls in BESIDE else None
+        in_force = shape_of(entries.pop(named(cls), None)) or other or shape_of(entries.get(key))
+        times, sizes = search_range(op, dim, dt, cls, in_force)
         if not times:
             continue
-        beside = BESIDE.get(cls)
-        e = range_entry(times, sizes, cls, entries.get(key if beside == "large" else f"{beside}/{key}") if beside else None)
-        if e:
-            entries[name] = e
-        print(json.dumps({name: e}), flush=True)
+        e = range_entry(times, sizes, cls, in_force)
+        if shape_of(e) != other:
+            entries[named(cls)] = e
+        print(json.dumps({named(cls): entries.get(named(cls))}), flush=True)
 
 
 SMALL_GRID_CAPS = (0, 2048)

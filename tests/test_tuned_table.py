@@ -22,15 +22,13 @@ def check(key, e):
     last = "grid_per_cu" if key.startswith("batch/") else "grid_cap"
     lead, *rest = e["top5"]
     assert [e["block"], e["ppt"], e[last], e["nt"]] == lead[2], key
-    # nothing recorded has both a mean lower by more than the margin and a lower worst case
-    assert all(lead[0] <= m * 1.005 + 1e-4 for m, _, _ in rest)
-    assert all(lead[1] <= w + 1e-4 for m, w, _ in rest if m * 1.005 < lead[0] - 1e-4)
+    assert all(lead[0] <= m * (1 + tune.KEEP_MARGIN) + 2e-4 for m, _, _ in rest), key
     if last == "grid_per_cu":
         assert len(e["ms"]) == len(e["n"]) == len(tune.BATCH_LISTS)
         return
     cls = key.split("/")[0] if key.count("/") == 3 else "large"
-    level, bound, sizes, caps = tune.CLASSES[cls]
-    assert len(e["us"]) == len(e["sizes"]) and set(e["sizes"]) <= set(sizes) and e["grid_cap"] in caps
+    level, bound, sizes = tune.CLASSES[cls]
+    assert len(e["us"]) == 2 * len(e["sizes"]) and set(e["sizes"]) <= set(sizes)
     assert level == 2 or e["min_n" if level == 3 else "max_n"] == bound
 
 
@@ -43,12 +41,29 @@ def test_rank_takes_the_steadiest_of_the_near_equal():
     assert len(rows) == 4
 
 
-def test_entries_beside_another_have_to_gain():
-    times = {(64, 1, 0, 1): [1.0, 1.0], (128, 1, 0, 1): [1.005, 1.005], (256, 1, 0, 1): [1.2, 1.2]}
-    beside = {"block": 128, "ppt": 1, "grid_cap": 0, "nt": 1}
-    assert tune.range_entry(times, [10, 20], "tiny", beside) is None
-    e = tune.range_entry(times, [10, 20], "tiny", dict(beside, block=256))
-    assert (e["block"], e["max_n"]) == (64, tune.CLASSES["tiny"][1])
+def test_the_shape_in_force_stays_within_the_margin():
+    a, b = (64, 1, 0, 1), (128, 1, 0, 1)
+    for slower, kept in ((1.029, b), (1.031, a)):
+        times = {a: [1.0, 1.0], b: [slower, slower]}
+        assert tune.rank(times, b)[0][2] == kept and tune.rank(times)[0][2] == a
+
+
+def test_classes_without_a_shape_of_their_own_get_no_entry(monkeypatch):
+    a, b = (64, 1, 0, 1), (128, 1, 0, 1)
+    seen = {}
+
+    def search(op, dim, dt, cls, in_force=None):
+        seen[cls] = in_force
+        gain = {"tiny": 1.1, "small": 1.01, "large": 1.0, "huge": 1.02}[cls]  # b's time over a's
+        return {a: [1.0, 1.0], b: [gain, gain]}, [10]
+
+    monkeypatch.setattr(tune, "search_range", search)
+    entry = {"block": 128, "ppt": 1, "grid_cap": 0, "nt": 1}
+    entries = {"flux/2/f64": dict(entry), "huge/flux/2/f64": dict(entry, block=512)}
+    tune.tune_range("flux", 2, "f64", entries)
+    assert seen == {"large": b, "huge": (512, 1, 0, 1), "small": b, "tiny": b}
+    assert {k: tune.shape_of(e) for k, e in entries.items()} == {
+        "flux/2/f64": b, "huge/flux/2/f64": a, "small/flux/2/f64": b, "tiny/flux/2/f64": a}
 
 
 def test_table_round_trip_of_all_classes(tmp_path):
@@ -100,8 +115,10 @@ def test_range_tuning_times_every_size_and_lifts_other_entries(monkeypatch):
         times, sizes = tune.search_range(op, dim, dt, "small")
         assert sizes == list(tune.CLASSES["small"][2])
         assert tune.rank(times)[0][2] in {(256, 1, 0, 1), (256, 1, 0, 0)}
-        assert {n for n, _ in seen} == set(sizes) and all(len(t) == len(sizes) for t in times.values())
-        assert (1024, 4, 2048, 1) not in times and (1024, 4, 2048, 1) in {c for _, c in seen}
+        assert {n for n, _ in seen} == set(sizes) and all(len(t) == 2 * len(sizes) for t in times.values())
+        assert (1024, 4, 0, 1) not in times and (1024, 4, 0, 1) in {c for _, c in seen}
+        times, _ = tune.search_range(op, dim, dt, "small", (1024, 4, 2048, 1))
+        assert (1024, 4, 2048, 1) in times
         assert F.fdbb_get_small_launch_config(op, dim, code) == small
     finally:
         tune.one_entry(op, dim, code)
