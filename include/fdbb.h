@@ -25,6 +25,12 @@
  * or FDBB_F32 (float).  Arithmetic is FP64 in both cases; FP32 values are
  * widened exactly on load and rounded to nearest on store.
  *
+ * Results are the same bits whenever a call is repeated.  Calls of other
+ * sizes, row alignments or launch configurations, and batches in other lists,
+ * may be evaluated by another compilation of the same formulas, whose
+ * contracted operations differ: equal points then agree within rounding, not
+ * always in the last bit.
+ *
  * ---------------------------------------------------------------- contract
  * Ownership: the caller owns every buffer; no entry point allocates or frees
  * memory, except the batch plans below, which own their descriptor tables
@@ -300,7 +306,7 @@ int fdbb_kernel_info(int op, int dim, int dtype, int ppt, int nontemporal, int *
                      int *scratch_bytes);
 
 /* ---------------------------------------------------------------- batches
- * Many independent blocks of uneven size in one persistent launch.  A task
+ * Many independent blocks of uneven size in one launch.  A task
  * names one operation on one field-set group; its fields mean what the
  * matching single-call entry point's arguments mean:
  *   in0  = U (V for prim2cons, W for char2cons), in1 = Fbar (adjoint only),
@@ -346,10 +352,11 @@ typedef struct fdbb_batch_plan fdbb_batch_plan;
  * streaming (1: the nt bit) or streaming device-coherent (2: nt and sc1)
  * output stores.  block == 0 takes the batch configuration installed for
  * the first task's storage type (FDBB_F64 for an empty list; see
- * fdbb_set_batch_config) and ignores ppt, grid and nontemporal; that
- * configuration is meant for lists that all write blocks (fused passes and
- * flux Jacobians of one dim and storage type), and other lists then run in a
- * shape that suits them.  Tasks that
+ * fdbb_set_batch_config) and ignores ppt, grid and nontemporal; kernel and
+ * shape then follow the list: lists that all write blocks (fused passes and
+ * flux Jacobians of one dim and storage type) have a kernel of their own, run
+ * in that configuration, other lists run in a shape that suits them.  A plan
+ * of explicit shape always launches in it.  Tasks that
  * overlap one another's outputs are rejected (FDBB_EALIAS).  Jacobian
  * staging needs LDS; a plan holds what its first task list needs, or, when
  * created with ntasks == 0, what any task needs (later task lists needing
@@ -395,7 +402,10 @@ int fdbb_get_batch_config(int dtype, int *block, int *ppt, int *grid_per_cu, int
 int fdbb_set_server_batch_config(int block, int ppt, int grid_per_cu, int nontemporal);
 int fdbb_get_server_batch_config(int *block, int *ppt, int *grid_per_cu, int *nontemporal);
 
-/* The launch configuration a plan was created with (any may be NULL). */
+/* The launch configuration a plan was created with (any may be NULL): what a
+ * plan of explicit shape launches with (its grid cut to the list's tiles), and
+ * what a captured launch does; with block == 0 a list's own launch may differ
+ * (see fdbb_batch_plan_create). */
 int fdbb_batch_plan_config(const fdbb_batch_plan *plan, int *block, int *ppt, int *grid,
                            int *nontemporal);
 
@@ -407,7 +417,7 @@ int fdbb_batch_plan_info(const fdbb_batch_plan *plan, int64_t *points, int64_t *
 int fdbb_batch_plan_destroy(fdbb_batch_plan *plan);
 
 /* For callers that cannot allocate device memory (tight serving loops,
- * harnesses that forbid hipMalloc): one persistent batch launch of `tasks`
+ * harnesses that forbid hipMalloc): one batch launch of `tasks`
  * with the meaning of fdbb_batch_plan_create + fdbb_batch_exec(use_graph =
  * 0), without a plan.  Allocates nothing: the task table goes into a fixed
  * device array of the library, one per device (about 230 KB, held until the

@@ -6,7 +6,7 @@
  * output pointers and leading dimensions are ignored on submission.  A
  * scheduler thread admits queued requests in arrival order while a launch
  * slot is free and their outputs fit in the server's device arena (the HBM
- * budget), runs every request admitted into a slot as one persistent batch
+ * budget), runs every request admitted into a slot as one batch
  * launch (FDBB_SERVE_BATCHED: continuous batching, one stream per slot,
  * launched with the configuration of fdbb_set_server_batch_config) or
  * each as its own launch on one stream (FDBB_SERVE_SINGLE: the

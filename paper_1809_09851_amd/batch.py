@@ -1,9 +1,11 @@
-"""Batches: many independent blocks of uneven size in one persistent launch.
+"""Batches: many independent blocks of uneven size in one launch.
 
-A ``Plan`` wraps ``fdbb_batch_plan_*``: the task table lives on the device,
-one persistent kernel walks every tile of every task, and that launch is
-captured once in a HIP graph and replayed.  ``run_noalloc`` is the same
-launch without a plan (``fdbb_batch_run_noalloc``: the table goes into the
+A ``Plan`` wraps ``fdbb_batch_plan_*``: the task table lives on the device and
+one kernel launch covers every tile of every task.  The launch of the plan's
+first list is captured in a HIP graph, which ``run`` replays for every list
+that wants the same launch; for other lists, and for a plan created empty, it
+launches directly.  A run that is recorded by a capture of the caller's takes
+any later list.  ``run_noalloc`` is the same launch without a plan (``fdbb_batch_run_noalloc``: the table goes into the
 library's fixed device array, nothing is allocated).  Task builders take
 the same tensors as the single-call functions in ``fdbb``.
 """
@@ -122,7 +124,7 @@ MAX_NOALLOC_TASKS = 1024  # FDBB_NOALLOC_MAX_TASKS
 
 
 def run_noalloc(tasks, block=0, ppt=1, grid=0, nontemporal=1, stream=None):
-    """One persistent launch of ``tasks`` through the allocation-free entry
+    """One launch of ``tasks`` through the allocation-free entry
     point (at most MAX_NOALLOC_TASKS tasks); ``block=0`` takes the installed
     batch configuration, as for plans."""
     arr = (F.Task * max(1, len(tasks)))(*tasks)
@@ -133,8 +135,9 @@ def run_noalloc(tasks, block=0, ppt=1, grid=0, nontemporal=1, stream=None):
 class Plan:
     """Owner of one ``fdbb_batch_plan``.  ``block=0`` (the default) takes the
     autotuned batch configuration installed for the first task's storage
-    type (``fdbb_set_batch_config``); an explicit block uses the given
-    ``ppt``, ``grid`` and ``nontemporal``."""
+    type (``fdbb_set_batch_config``), and kernel and shape that suit each
+    list; an explicit block uses the given ``ppt``, ``grid`` and
+    ``nontemporal`` for every list."""
 
     def __init__(self, tasks, capacity=None, block=0, ppt=1, grid=0, nontemporal=1):
         lib = F.library()
@@ -146,7 +149,9 @@ class Plan:
         self.block, self.ppt, self.grid, self.nontemporal = self.config()
 
     def config(self):
-        """(block, ppt, grid, nontemporal) the plan launches with."""
+        """(block, ppt, grid, nontemporal) the plan was created with.  A plan
+        of explicit shape launches in it, with at most that grid; with
+        ``block=0`` a list may take another kernel and shape."""
         b, p, g, t = ctypes.c_int(), ctypes.c_int(), ctypes.c_int(), ctypes.c_int()
         F.check(F.library().fdbb_batch_plan_config(self._h, ctypes.byref(b), ctypes.byref(p), ctypes.byref(g),
                                                    ctypes.byref(t)))

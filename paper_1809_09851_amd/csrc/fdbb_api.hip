@@ -1,6 +1,6 @@
 // C ABI of the library (declared in include/fdbb.h): host-side validation,
 // launch configuration, kernel launches on the caller's stream, and the
-// persistent batch plans with their HIP graphs.
+// batch plans with their HIP graphs.
 #include "../../include/fdbb.h"
 
 #include <algorithm>
@@ -160,7 +160,7 @@ Config get_config(int op, int dim, int dtype, int64_t n, bool *own = nullptr)
     return unpack(g_level_cfg[level][op][dim - 1][dtype].load(std::memory_order_relaxed));
 }
 
-// Launch configuration of the persistent batch kernel, per storage type:
+// Launch configuration of the batch kernels, per storage type:
 // what plans created with block == 0 (and the request server's plans) use.
 // grid_per_cu 0 sizes the grid to 2048 / block workgroups per compute unit.
 struct BatchConfig {
@@ -655,9 +655,6 @@ int begin(Call &c, int op, int dim, double gamma, int dtype, int64_t n)
     return FDBB_OK;
 }
 
-// Fills c for any op from the task-style argument list; shared by the
-// single-call entry points and the batch plans.  `mode` selects R (1) or L
-// (0) for the characteristic products.
 // Whether in0 and in1 are views of the same K rows, shifted by so few points
 // that what one side read is still cached when the other asks for it: the
 // lines of that distance, a quarter of the last-level cache at most.  Roe
@@ -673,6 +670,9 @@ bool near_views(const fdbb_task &t, int K)
     return shift < t.n * (int64_t)elem_size(t.dtype) && shift * K <= kNearBytes;
 }
 
+// Fills c for any op from the task-style argument list; shared by the
+// single-call entry points and the batch plans.  `mode` selects R (1) or L
+// (0) for the characteristic products.
 int build_call(Call &c, const fdbb_task &t, int mode = 0)
 {
     int rc = begin(c, t.op, t.dim, t.gamma, t.dtype, t.n);
@@ -799,7 +799,7 @@ int build_call(Call &c, const fdbb_task &t, int mode = 0)
     return FDBB_OK;
 }
 
-// Ops a batch plan can run: everything the persistent kernel dispatches.
+// Ops a batch plan can run: everything the general batch kernel dispatches.
 // The eigenvector blocks and characteristic products have kernels of their
 // own, and the general EOS needs parameters a task does not carry.
 bool batchable(int op)

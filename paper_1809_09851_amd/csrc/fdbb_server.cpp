@@ -1,7 +1,7 @@
 // Native request server (declared in include/fdbb_server.h): a scheduler
 // thread admits queued requests in arrival order while a launch slot is free
 // and their outputs fit in a device arena of the budget's size, packs them
-// into one persistent batch launch per slot (a direct launch of the slot's
+// into one batch launch per slot (a direct launch of the slot's
 // plan, with the server's batch configuration and the LDS its list
 // stages), and retires them when the slot's completion event fires.  Outputs
 // live in the arena until the caller releases them.

@@ -7,13 +7,15 @@
 // not fit in the last-level cache, a 3D workgroup therefore writes one set of
 // its tile's parts (Split, chosen by split_of on the host): in FP64 one
 // direction's rows and blocks, in FP32, where a row's run is half as long,
-// one direction's blocks or all rows.  Spans of tiles go through one set
-// after the other, few waves are resident (the launch reserves LDS), and the
-// state that a later set reads again comes from the last-level cache.
-// Against one workgroup per tile at the best shape, on the same buffers: FP64
-// 1 000 003 points 145 -> 125 us, 4 000 037 541 -> 503 us, 2^24 2410 -> 2344
-// us (5.84 TB/s); FP32 4 000 037 points 283 -> 250 us, 12 000 017 839 -> 735
-// us (6.66 TB/s).
+// one direction's blocks or all rows, and that up to 512 MiB of blocks (1.79 M
+// points) only.  Spans of tiles go through one set after the other, few waves
+// are resident (the launch reserves LDS), and the state that a later set
+// reads again comes from the last-level cache.  FP32 beyond takes whole tiles
+// with few waves resident.  Against one workgroup per tile at the best shape,
+// on the same buffers: FP64 1 000 003 points 144 -> 125 us, 4 000 037 535 ->
+// 513 us, 2^24 2410 -> 2340 us (5.85 TB/s); FP32 apart 1 000 003 points 69 ->
+// 64 us, 1 500 001 105 -> 94 us, whole tiles 2 500 009 182 -> 178 us, 2^24
+// over three sets of arrays 1213 -> 1173 us.
 #include "fdbb_internal.hpp"
 
 namespace fdbb {

@@ -4,7 +4,7 @@ Requests (cons2prim, flux, flux Jacobian or adjoint over a view of a
 device-resident state, any dim, FP64 or FP32 storage) arrive over time.  A
 scheduler admits them in arrival order as soon as a launch slot is free and
 their outputs fit in the HBM budget, packs every admitted request of a tick
-into one persistent batch launch (one batch plan per slot, each slot on its
+into one batch launch (one batch plan per slot, each slot on its
 own stream), and retires requests when their slot's completion event fires,
 giving their bytes back to the budget.  Work of different slots overlaps on
 the device, so requests that arrive while others run are started as slots
